@@ -941,8 +941,7 @@ int bsi_reserve(bsi_handle h, const bsi_reserve_cfg* r) {
     partial = std::max(partial, (size_t)shear_blocks(sgi, np) * np * 6 * sizeof(double));
   size_t bias_part = 0, bias_mc = 0;
   if (r->bias) {
-    bias_part = std::max(bias_plan(std::max(sgi, 1), r->max_points, r->max_boot).partial_doubles,
-                         bias_plan(1 << 30, r->max_points, r->max_boot).partial_doubles) * sizeof(double);
+    bias_part = bias_partial_bound(r->max_points, r->max_boot) * sizeof(double);
     bias_mc = (size_t)(r->max_boot + 1) * 2 * sizeof(double);
   }
   const size_t stage = std::max(bsi_host::stage_size({S * 4, S * 8, S * 8, r->weighted ? S * 4 : 0}),

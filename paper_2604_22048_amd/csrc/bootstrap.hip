@@ -7,13 +7,14 @@
 // resamples) with the per-galaxy log-marginal tables E+ and E- [P x G]:
 //   Lp[r][p] = sum_n C[r][n] E[p][n],  p < 2P over [E+; E-].
 // The product runs on the FP64 matrix cores (v_mfma_f64_16x16x4f64): a
-// workgroup of 4 waves owns a 64 x 64 output tile (each wave 32 x 32, i.e.
-// 2 x 2 MFMA tiles) of one K split, stages 32 galaxies of C (converted to
-// float64) and of E per step in LDS, and writes its partial tile; a second
-// kernel adds the splits in order, forms each row's posterior mean of g on
-// the grid, and m_r, c_r; a third takes the standard deviations over the
-// resamples.  ell = -inf (a galaxy with no supported sample at that point)
-// is carried as -1e300 so that a galaxy not drawn (c = 0) adds exactly 0.
+// workgroup of 4 waves owns a 64 x 64 output tile (16 RT rows for few
+// resamples) of one K split, its waves taking every fourth chunk of 16
+// galaxies; the waves' sums are added through LDS and the partial tile is
+// written; a second kernel adds the splits in order, forms each row's
+// posterior mean of g on the grid, and m_r, c_r; a third takes the standard
+// deviations over the resamples.  ell = -inf (a galaxy with no supported
+// sample at that point) is carried as -1e300 so that a galaxy not drawn
+// (c = 0) adds exactly 0.
 #include <algorithm>
 
 #include "bsi_kernels.h"
@@ -25,81 +26,138 @@ namespace {
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTile = 64;     // output tile (rows r and columns p) per workgroup
-constexpr int kKc = 32;       // galaxies per LDS step
-constexpr int kLd = kKc + 1;  // padded LDS row (doubles)
+constexpr int kKc = 8;        // galaxies per chunk: 2 per lane group, one MFMA step each
+constexpr int kColTiles = kTile / 16;
 constexpr double kNegBig = -1e300;
+constexpr int kSplitTarget = 2304;   // workgroups of a product, about
+
+// Vector loads from rows that are only element-aligned (odd G).
+typedef int i32x2u __attribute__((ext_vector_type(2), aligned(4)));
+typedef double f64x2u __attribute__((ext_vector_type(2), aligned(8)));
 
 __device__ __forceinline__ f64x4 mfma_f64(double a, double b, f64x4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// Partial products of one K split.  Grid: x = column tiles, y = row tiles,
-// z = K splits.  out[z][r][p] for r < R, p < 2P.
-__global__ void __launch_bounds__(256) bias_gemm_kernel(const int32_t* __restrict__ counts,
-                                                        const double* __restrict__ ep,
-                                                        const double* __restrict__ em, int G, int P,
-                                                        int R, int k_per_split,
-                                                        double* __restrict__ out) {
-  __shared__ double As[kTile][kLd];   // C tile: rows r, galaxies k
-  __shared__ double Bs[kTile][kLd];   // E tile: columns p, galaxies k
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r0 = blockIdx.y * kTile, p0 = blockIdx.x * kTile;
-  const int k_begin = blockIdx.z * k_per_split;
-  const int k_end = min(G, k_begin + k_per_split);
+// 16-row tiles per workgroup tile for R rows: 4, or fewer where 4 would be padding.
+inline int row_tiles(int R) { return R > 32 ? 4 : R > 16 ? 2 : 1; }
+
+// One lane's operands of a chunk: 2 consecutive galaxies of each row and column.
+template <int RT>
+struct BiasChunk {
+  i32x2u a[RT];
+  f64x2u b[kColTiles];
+};
+
+// Partial products of one K split.  Grid: one workgroup per (output tile,
+// split), the split fastest, so that with a multiple of 8 splits an XCD works
+// on its own galaxies only; its workgroups go through them at about the same
+// pace, row tiles of one column tile next to each other, so the XCD's L2 holds
+// what they share.  out[z][r][p] for r < R, p < 2P.
+//
+// Bound by the FP64 matrix cores.  Lane (i, q) (i = lane % 16, q = lane / 16)
+// holds galaxies 2 q and 2 q + 1 of row i and column i of a chunk, so the
+// operands come from global memory as 8- and 16-byte loads without passing
+// LDS, the next two chunks' in flight during this chunk's MFMAs (8 RT of 64
+// cycles each), and no barrier stands between chunks.  501 x 2,178 x 10,000:
+// 485 us, 45 TFLOP/s of the 62.7 that a large float64 product reaches on this
+// card; staging 32 galaxies at a time through LDS between barriers took
+// 1,359 us.
+template <int RT>
+__global__ void __launch_bounds__(256, 2)
+    bias_gemm_kernel(const int32_t* __restrict__ counts, const double* __restrict__ ep,
+                     const double* __restrict__ em, int G, int P, int R, int k_per_split, int n_split,
+                     double* __restrict__ out) {
+  __shared__ f64x4 xs[2][RT * kColTiles][kWave];   // two waves' accumulators on their way to the other two
+  const int lane = lane_id(), wave = threadIdx.x / kWave;
+  const int split = blockIdx.x % n_split, tile = blockIdx.x / n_split;
+  const int n_rt = (R + 16 * RT - 1) / (16 * RT);
+  const int r0 = (tile % n_rt) * 16 * RT, p0 = (tile / n_rt) * kTile;
+  const int k_begin = split * k_per_split, k_end = min(G, k_begin + k_per_split);
   const int P2 = 2 * P;
-  const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;   // the wave's 32 x 32 sub-tile
-  const int li = lane & 15, lk = lane >> 4;
-  f64x4 acc[2][2];
+  const int i = lane & 15, q = lane >> 4;
+  // rows past R and columns past 2P read a valid one: their sums are not written
+  const int32_t* arow[RT];
+  const double* brow[kColTiles];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int t = 0; t < RT; ++t) arow[t] = counts + (int64_t)max(min(r0 + 16 * t + i, R - 1) - 1, 0) * G;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
-  for (int kc = k_begin; kc < k_end; kc += kKc) {
-    __syncthreads();
-    // stage 64 x 32 of C and of E (k fastest; zero outside the matrices)
-    for (int t = tid; t < kTile * kKc; t += 256) {
-      const int row = t / kKc, k = t - row * kKc;
-      const int n = kc + k;
-      double cv = 0.0, evv = 0.0;
-      if (n < k_end) {
-        const int r = r0 + row;
-        if (r < R) cv = (r == 0) ? 1.0 : (double)counts[(int64_t)(r - 1) * G + n];
-        const int p = p0 + row;
-        if (p < P2) {
-          const double v = (p < P) ? ep[(int64_t)p * G + n] : em[(int64_t)(p - P) * G + n];
-          evv = (v > kNegBig) ? v : kNegBig;   // -inf (and anything below) -> -1e300
-        }
-      }
-      As[row][k] = cv;
-      Bs[row][k] = evv;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k0 = 0; k0 < kKc; k0 += 4) {
-      const int k = k0 + lk;
-      double a[2], b[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) a[i] = As[wr + 16 * i + li][k];   // A[i = li][k = lk]
-#pragma unroll
-      for (int j = 0; j < 2; ++j) b[j] = Bs[wc + 16 * j + li][k];   // B[k = lk][j = li]
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = mfma_f64(a[i], b[j], acc[i][j]);
-    }
+  for (int t = 0; t < kColTiles; ++t) {
+    const int p = min(p0 + 16 * t + i, P2 - 1);
+    brow[t] = (p < P) ? ep + (int64_t)p * G : em + (int64_t)(p - P) * G;
   }
+  const bool ones = r0 + i == 0;    // row 0 of the product: every galaxy once
+  auto load = [&](int k) {
+    BiasChunk<RT> c;
+    const int n = k + 2 * q;
+    if (k + kKc <= k_end) {
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+        c.a[t] = counts ? *reinterpret_cast<const i32x2u*>(arow[t] + n) : i32x2u{0, 0};
+#pragma unroll
+      for (int t = 0; t < kColTiles; ++t) c.b[t] = *reinterpret_cast<const f64x2u*>(brow[t] + n);
+    } else {                          // the split's last galaxies: zeros past k_end
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const bool in = n + j < k_end;
+#pragma unroll
+        for (int t = 0; t < RT; ++t) c.a[t][j] = in && counts ? arow[t][n + j] : 0;
+#pragma unroll
+        for (int t = 0; t < kColTiles; ++t) c.b[t][j] = in ? brow[t][n + j] : 0.0;
+      }
+    }
+    return c;
+  };
+  f64x4 acc[RT][kColTiles];
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int u = 0; u < kColTiles; ++u) acc[t][u] = f64x4{0.0, 0.0, 0.0, 0.0};
+  int k = k_begin + kKc * wave;
+  BiasChunk<RT> c = load(k), c1 = load(k + 4 * kKc);
+  for (; k < k_end; k += 4 * kKc) {
+    const BiasChunk<RT> c2 = load(k + 8 * kKc);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      double a[RT], b[kColTiles];
+#pragma unroll
+      for (int t = 0; t < RT; ++t) a[t] = (t == 0 && ones) ? 1.0 : (double)c.a[t][j];
+      // -inf (and anything below) -> -1e300
+#pragma unroll
+      for (int u = 0; u < kColTiles; ++u) b[u] = (c.b[u][j] > kNegBig) ? c.b[u][j] : kNegBig;
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int u = 0; u < kColTiles; ++u) acc[t][u] = mfma_f64(a[t], b[u], acc[t][u]);
+    }
+    c = c1;
+    c1 = c2;
+  }
+  // waves 2, 3 -> 0, 1, then wave 1 -> 0
+#pragma unroll
+  for (int h = 2; h >= 1; h >>= 1) {
+    __syncthreads();
+    if (wave >= h && wave < 2 * h)
+#pragma unroll
+      for (int t = 0; t < RT * kColTiles; ++t) xs[wave - h][t][lane] = acc[t / kColTiles][t % kColTiles];
+    __syncthreads();
+    if (wave < h)
+#pragma unroll
+      for (int t = 0; t < RT * kColTiles; ++t) acc[t / kColTiles][t % kColTiles] += xs[wave][t][lane];
+  }
+  if (wave != 0) return;
   // D[i][j] of a 16 x 16 float64 tile sits in lane j + 16 (i % 4), element
   // i / 4 (rows interleaved across the lane groups, unlike the float32 form)
-  double* o = out + (int64_t)blockIdx.z * R * P2;
+  double* o = out + (int64_t)split * R * P2;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int t = 0; t < RT; ++t)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int u = 0; u < kColTiles; ++u)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int r = r0 + wr + 16 * i + lk + 4 * e;
-        const int p = p0 + wc + 16 * j + li;
-        if (r < R && p < P2) o[(int64_t)r * P2 + p] = acc[i][j][e];
+        const int r = r0 + 16 * t + q + 4 * e;
+        const int p = p0 + 16 * u + i;
+        if (r < R && p < P2) o[(int64_t)r * P2 + p] = acc[t][u][e];
       }
 }
 
@@ -213,14 +271,22 @@ __global__ void __launch_bounds__(kMeanThreads) bias_stats_kernel(const double* 
 BiasPlan bias_plan(int G, int P, int n_boot) {
   BiasPlan b;
   b.R = n_boot + 1;
-  const int tiles = ((2 * P + kTile - 1) / kTile) * ((b.R + kTile - 1) / kTile);
-  // enough K splits for about two workgroups per compute unit, each at least 4 LDS steps
-  int splits = std::max(1, (512 + tiles - 1) / tiles);
-  splits = std::min(splits, std::max(1, G / (4 * kKc)));
+  const int tiles = ((2 * P + kTile - 1) / kTile) * ((b.R + 16 * row_tiles(b.R) - 1) / (16 * row_tiles(b.R)));
+  // about kSplitTarget workgroups (4.5 rounds of two per compute unit, so that
+  // the last round is a small share), each with at least four chunks per wave;
+  // from 8 splits on a multiple of 8, one XCD's galaxies each
+  int splits = std::max(1, std::min((kSplitTarget + tiles / 2) / tiles, G / (16 * kKc)));
+  if (splits >= 8) splits = splits / 8 * 8;
   b.k_per_split = ((G + splits - 1) / splits + kKc - 1) / kKc * kKc;
   b.n_split = std::max(1, (G + b.k_per_split - 1) / b.k_per_split);
   b.partial_doubles = (size_t)b.n_split * b.R * 2 * P;
   return b;
+}
+
+size_t bias_partial_bound(int P, int n_boot) {
+  // n_split tiles <= kSplitTarget + tiles, a tile at most 64 x 64 values
+  const size_t rows = (size_t)(n_boot + kTile) / kTile * kTile, cols = (size_t)(2 * P + kTile - 1) / kTile * kTile;
+  return (size_t)kSplitTarget * kTile * kTile + rows * cols;
 }
 
 size_t bias_mean_lds_bytes(int P) { return sizeof(double) * 2 * (size_t)P; }
@@ -228,9 +294,11 @@ size_t bias_mean_lds_bytes(int P) { return sizeof(double) * 2 * (size_t)P; }
 hipError_t launch_bias(const BiasPlan& b, const int32_t* counts, const double* ep, const double* em,
                        int G, int P, const double* gpts, double g_abs, double* partial, double* gmean,
                        double* mc, double* stats, hipStream_t s) {
-  const dim3 grid((2 * P + kTile - 1) / kTile, (b.R + kTile - 1) / kTile, b.n_split);
-  hipLaunchKernelGGL(bias_gemm_kernel, grid, dim3(256), 0, s, counts, ep, em, G, P, b.R,
-                     b.k_per_split, partial);
+  const int rt = row_tiles(b.R);
+  const int tiles = ((2 * P + kTile - 1) / kTile) * ((b.R + 16 * rt - 1) / (16 * rt));
+  auto gemm = rt == 4 ? bias_gemm_kernel<4> : rt == 2 ? bias_gemm_kernel<2> : bias_gemm_kernel<1>;
+  hipLaunchKernelGGL(gemm, dim3(tiles * b.n_split), dim3(256), 0, s, counts, ep, em, G, P, b.R,
+                     b.k_per_split, b.n_split, partial);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const size_t lds = bias_mean_lds_bytes(P);

@@ -186,6 +186,8 @@ struct BiasPlan {
   size_t partial_doubles;   // n_split x R x 2 P
 };
 BiasPlan bias_plan(int G, int P, int n_boot);
+// At least partial_doubles of every plan with at most P points and n_boot resamples.
+size_t bias_partial_bound(int P, int n_boot);
 size_t bias_mean_lds_bytes(int P);
 hipError_t launch_bias(const BiasPlan& b, const int32_t* counts, const double* ep, const double* em,
                        int G, int P, const double* gpts, double g_abs, double* partial, double* gmean,
