@@ -1,10 +1,9 @@
-// Multi-chain effective sample size and R-hat of one parameter, computed by
-// one whole workgroup of 256 threads (Section 4.1 diagnostics):
+// Multi-chain effective sample size of one parameter, computed by one whole
+// workgroup of 256 threads (Section 4.1 diagnostics; the request server's
+// check, where one request's six parameters are all there is to do):
 // autocorrelations combined across chains, Geyer's initial monotone
 // sequence of pair sums, no rank normalisation, tau floored at
-// 1 / log10(M n) (so ESS <= M n log10(M n)); classic R-hat; optionally the
-// split R-hat (each chain cut into its first and last floor(n/2) draws, the
-// classic statistic over the 2M halves).  The M x n draws
+// 1 / log10(M n) (so ESS <= M n log10(M n)).  The M x n draws
 // are staged in LDS as float64.  Chain means and variances are block
 // reductions; lags are computed 64 at a time (each lag's sum split over the
 // four waves by draw index mod 4, partials added in wave order) until the
@@ -16,7 +15,7 @@
 namespace bsi {
 
 struct EssShared {
-  double mean_c[32], var_c[32];
+  double mean_c[16], var_c[16];
   double part[4][64];   // per-wave partials (block sums, lag sums)
   double rho[64];
   double W, vp;
@@ -66,33 +65,15 @@ __device__ inline double rhat_from_moments(const double* mean, const double* var
 
 // Draw s of chain c: src[(c * stride + s) * P + par], c < C <= 16, s < n,
 // n >= 2.  xs: LDS double[C n]; es: LDS scratch.  Every thread of the
-// workgroup must call; the results are valid in thread 0.
-// With rsplit non-NULL (and n >= 4) the split R-hat is also computed (thread 0).
+// workgroup must call; the result is valid in thread 0.
 __device__ inline void ess_one_param(const float* __restrict__ src, int C, int n, int stride, int P,
-                                     int par, double* xs, EssShared& es, float& ess_out,
-                                     float& rhat_out, float* rsplit = nullptr) {
+                                     int par, double* xs, EssShared& es, float& ess_out) {
   const int tid = threadIdx.x;
   for (int t = tid; t < C * n; t += blockDim.x) {
     const int c = t / n, s = t - c * n;
     xs[t] = (double)src[((int64_t)c * stride + s) * P + par];
   }
   __syncthreads();
-  if (rsplit && n >= 4) {
-    // halves: draws [0, h) and [n - h, n) of each chain (the middle one of an odd n dropped)
-    const int h = n / 2;
-    for (int c = 0; c < C; ++c)
-      for (int k = 0; k < 2; ++k) {
-        double m, v;
-        ess_block_moments(xs + c * n + k * (n - h), h, es, m, v);
-        if (tid == 0) {
-          es.mean_c[2 * c + k] = m;
-          es.var_c[2 * c + k] = v;
-        }
-      }
-    __syncthreads();
-    if (tid == 0) *rsplit = (float)rhat_from_moments(es.mean_c, es.var_c, 2 * C, h);
-    __syncthreads();
-  }
   for (int c = 0; c < C; ++c) {
     double m, v;
     ess_block_moments(xs + c * n, n, es, m, v);
@@ -158,7 +139,6 @@ __device__ inline void ess_one_param(const float* __restrict__ src, int C, int n
     double tau = (vp > 0.0 && tau_sum > 0.0) ? -1.0 + 2.0 * tau_sum : 1.0;
     tau = fmax(tau, 1.0 / log10(m));
     ess_out = (vp > 0.0) ? (float)(m / tau) : (float)m;
-    rhat_out = (float)sqrt(vp / W);
   }
   __syncthreads();   // xs and es may be reused by the caller
 }

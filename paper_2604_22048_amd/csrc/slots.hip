@@ -94,8 +94,8 @@ slots_check_kernel(const int32_t* __restrict__ list, int C, int W, int S, int ev
     }
     return;
   }
-  float e = 0.f, r = 0.f;
-  ess_one_param(samples + (int64_t)slot * C * S * 6, C, n, S, 6, par, xs, es, e, r);
+  float e = 0.f;
+  ess_one_param(samples + (int64_t)slot * C * S * 6, C, n, S, 6, par, xs, es, e);
   if (threadIdx.x == 0) {
     sa.ess6[(int64_t)slot * 6 + par] = e;
     __threadfence();

@@ -1,0 +1,57 @@
+"""bsi_ess at the edges of its layout: blocks of 16 draws, 1,024 draws per wave
+pass, 16 lags per pass over the chains, parameters per workgroup."""
+import numpy as np
+import pytest
+
+from oracle import diagnostics
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def bsi(device):
+    from paper_2604_22048_amd import api
+    return api
+
+
+# (galaxies, chains, draws, parameters, memory of the chains in draws)
+SHAPES = [(3, 1, 4, 1, 0), (2, 16, 15, 6, 0), (2, 2, 16, 5, 1), (3, 4, 17, 9, 2), (1, 4, 1024, 6, 3),
+          (2, 2, 1041, 7, 40), (1, 3, 2500, 6, 200), (1, 1, 18944, 2, 30)]
+
+
+@pytest.mark.parametrize("G,C,S,P,memory", SHAPES)
+def test_ess_layout_edges(bsi, G, C, S, P, memory):
+    """Every float64 sum here is good to about 1e-13 of its value, so what is left
+    of the difference is the float32 rounding of the result (2^-24; twice that
+    allowed)."""
+    import torch
+    rng = np.random.default_rng(G + 100 * C + 1000 * S)
+    x = rng.normal(size=(G, C, S + 4 * memory, P))
+    if memory:
+        r = np.exp(-1.0 / memory)
+        for t in range(1, x.shape[2]):
+            x[:, :, t] += r * x[:, :, t - 1]
+    x = (x[:, :, 4 * memory:] + rng.normal(size=(G, C, 1, P)) * 0.05 + 3.0).astype(np.float32)
+    e, r, rs = [a.cpu().numpy().astype(np.float64) for a in bsi.ess(torch.tensor(x).cuda(), split=True)]
+    e2 = bsi.ess(torch.tensor(x).cuda())[0].cpu().numpy()
+    assert np.array_equal(e2, e.astype(np.float32))
+    tol = 2.0 ** -23
+    for g in range(G):
+        for p in range(P):
+            y = x[g, :, :, p].astype(np.float64)
+            assert abs(e[g, p] / diagnostics.ess(y) - 1) < tol
+            if C > 1:
+                assert abs(r[g, p] / diagnostics.rhat(y) - 1) < tol
+            assert abs(rs[g, p] / diagnostics.split_rhat(y) - 1) < tol
+
+
+def test_ess_constant_chains(bsi):
+    """No variance at all: the number of draws; no variance within the chains
+    only: every lag is taken, to the last pair."""
+    import torch
+    x = torch.zeros(2, 2, 100, 2)
+    x[1, 1] = 0.5
+    e, _ = bsi.ess(x.cuda())
+    assert torch.all(e[0] == 200)
+    # rho = 1 at every lag: tau = -1 + 2 (2 S / 2) = 199
+    assert torch.allclose(e[1].cpu(), torch.full((2,), 200 / 199.0), rtol=2.0 ** -23)
