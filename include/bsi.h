@@ -150,9 +150,8 @@ const char* bsi_last_error(bsi_handle h);
  *     The graph reads the handle's workspace and staging buffer at every
  *     replay: until it is destroyed, use the handle for no other call
  *     (one handle per live graph), and replay it after bsi_reserve only if
- *     that reserve came first.  bsi_hmc_sample under capture ignores
- *     use_graph and records its trajectory launches (the stamp sizes in
- *     sequence) into the caller's graph.
+ *     that reserve came first.  bsi_hmc_sample under capture records
+ *     its launches (the stamp sizes in sequence) into the caller's graph.
  *   - bsi_autotune, bsi_autotune_transform and the slot server allocate
  *     their own buffers and are not for capture.
  */
@@ -285,10 +284,11 @@ typedef struct {
   float jitter;              /* relative step-size jitter in [0, 1) [0 = none]             */
   int32_t form;              /* BSI_FORM_BATCHED: all galaxies per launch;
                                 BSI_FORM_PLAIN: one galaxy and one leapfrog step per launch */
-  int32_t iters_per_launch;  /* batched form: trajectories per kernel launch (>= 1)        */
-  int32_t use_graph;         /* batched form: 1 = replay each launch round from a captured
-                                HIP graph (the stamp sizes' launches in sequence on one
-                                stream); 0 = direct launches, the sizes concurrently on
+  int32_t iters_per_launch;  /* batched form: trajectories per kernel launch at least (>= 1);
+                                the library takes more where a launch would be short (512
+                                evaluations); the samples do not depend on it               */
+  int32_t use_graph;         /* accepted and without effect: a call's launches are few enough
+                                to be enqueued directly, the stamp sizes concurrently on
                                 forked streams                                             */
   uint64_t seed;             /* Philox key                                                 */
   uint64_t uid_base;         /* chain uid = uid_base + galaxy * n_chains + chain           */

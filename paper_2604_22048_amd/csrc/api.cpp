@@ -142,32 +142,47 @@ const int32_t* ggidx_ptr(bsi_handle h, const Plan& p, const ClassRange& c) {
   return static_cast<const int32_t*>(p.E > 1 ? h->ggidx.p : h->gidx.p) + c.gbegin;
 }
 
-// Per-bin noise weights (sqrt w beside the spectrum, which is whitened) for
-// batches with several exposures or correlated noise.
-int noise_weights(bsi_handle h, const bsi_batch* b, const Plan& p, hipStream_t s) {
-  for (const ClassRange& c : p.classes) {
-    hipError_t e = launch_whiten(b->noise_ps, gidx_ptr(h, c), c.count,
-                                 static_cast<const int64_t*>(h->off.p),
-                                 static_cast<const int64_t*>(h->bin_off.p), c.N, c.P,
-                                 static_cast<float2*>(h->dh.p), static_cast<float*>(h->sqw.p), s);
-    if (e != hipSuccess) return hip_fail(h, e, "noise weights launch");
-  }
-  return BSI_OK;
+// Per-bin noise weights (sqrt w beside the spectrum, which is whitened) of one
+// size class of a batch with several exposures or correlated noise.
+hipError_t class_weights(bsi_handle h, const bsi_batch* b, const ClassRange& c, hipStream_t s) {
+  return launch_whiten(b->noise_ps, gidx_ptr(h, c), c.count, static_cast<const int64_t*>(h->off.p),
+                       static_cast<const int64_t*>(h->bin_off.p), c.N, c.P, static_cast<float2*>(h->dh.p),
+                       static_cast<float*>(h->sqw.p), s);
 }
 
 inline bool weighted(const bsi_batch* b) { return b->n_exp > 1 || b->noise_ps != nullptr; }
 
-int data_spectrum(bsi_handle h, const bsi_batch* b, const Plan& p, const float* data,
-                  const double* model, double* chi2, hipStream_t s) {
-  for (const ClassRange& c : p.classes) {
-    hipError_t e = launch_stamp_dft(transform_of(h, c.N) == BSI_TRANSFORM_MFMA, data, model,
-                                    gidx_ptr(h, c), c.count, static_cast<const int64_t*>(h->off.p),
-                                    static_cast<const int64_t*>(h->bin_off.p), c.N, c.P,
-                                    static_cast<float2*>(h->dh.p), chi2, s);
-    if (e != hipSuccess) return hip_fail(h, e, "dft_bins launch");
-  }
-  return BSI_OK;
+// The data spectra (model: of data - model, with its chi2) of one size class.
+hipError_t class_spectrum(bsi_handle h, const ClassRange& c, const float* data, const double* model,
+                          double* chi2, hipStream_t s) {
+  return launch_stamp_dft(transform_of(h, c.N) == BSI_TRANSFORM_MFMA, data, model, gidx_ptr(h, c), c.count,
+                          static_cast<const int64_t*>(h->off.p), static_cast<const int64_t*>(h->bin_off.p), c.N,
+                          c.P, static_cast<float2*>(h->dh.p), chi2, s);
 }
+
+// Run fn(class, stream) for every size class: the classes concurrently on
+// forked streams, or under capture in sequence on s (capturing the fork/join
+// has ended in a host segmentation fault inside the call, cause not
+// identified, so it is never captured).
+template <typename F>
+hipError_t for_classes(bsi_handle h, const Plan& p, hipStream_t s, bool cap, F&& fn) {
+  const int n = (int)p.classes.size();
+  if (!cap)
+    return fork_join(h, s, n, [&](int i, hipStream_t st) { return fn(p.classes[i], st); }, [&](int i) {
+      const ClassRange& c = p.classes[i];
+      return (double)c.N * c.N * c.gcount;    // the class's share of the work
+    });
+  hipError_t e = hipSuccess;
+  for (int i = 0; e == hipSuccess && i < n; ++i) e = fn(p.classes[i], s);
+  return e;
+}
+
+// Leapfrog evaluations of a chain per launch, about: a launch costs 6 us plus
+// the galaxy's staging (its spectrum, the PSF table in float64, the chain
+// states), 10 % of a 20-step trajectory of a single 53-pixel galaxy, and an
+// evaluation 2 to 20 us, so that a workgroup still ends within about 10 ms and
+// other streams' work gets onto the device.  The samples do not depend on it.
+constexpr int kLaunchEvals = 512;
 
 // Every workspace buffer of a handle (an array: an initializer_list returned
 // from a function would refer to a temporary that dies with the return).
@@ -387,8 +402,11 @@ int bsi_loglik_grad(bsi_handle h, const bsi_batch* batch, const float* data, con
     model = static_cast<const double*>(h->model.p);
     chi2 = static_cast<double*>(h->chi2.p);
   }
-  if ((rc = data_spectrum(h, batch, p, data, model, chi2, s))) return rc;
-  if (mx && (rc = noise_weights(h, batch, p, s))) return rc;
+  for (const ClassRange& c : p.classes) {
+    hipError_t e = class_spectrum(h, c, data, model, chi2, s);
+    if (e == hipSuccess && mx) e = class_weights(h, batch, c, s);
+    if (e != hipSuccess) return hip_fail(h, e, "data spectrum launch");
+  }
   for (const ClassRange& c : p.classes) {
     hipError_t e = launch_loglik(static_cast<const float2*>(h->dh.p),
                                  static_cast<const int64_t*>(h->bin_off.p), ggidx_ptr(h, p, c),
@@ -463,8 +481,6 @@ int bsi_hmc_sample(bsi_handle h, const bsi_batch* batch, const float* data, cons
                     pb.stage())))
     return rc;
   if ((rc = upload_plan(h, batch, p, s, cap))) return rc;
-  if ((rc = data_spectrum(h, batch, p, data, nullptr, nullptr, s))) return rc;
-  if (mx && (rc = noise_weights(h, batch, p, s))) return rc;
 
   HmcArgs a{};
   a.dh = static_cast<const float2*>(h->dh.p);
@@ -510,99 +526,43 @@ int bsi_hmc_sample(bsi_handle h, const bsi_batch* batch, const float* data, cons
   a.nuts = nuts ? 1 : 0;
   a.max_depth = cfg->max_tree_depth;
 
-  for (const ClassRange& c : p.classes) {
+  const int T = a.t_stop;
+  const bool plain = cfg->form == BSI_FORM_PLAIN;
+  // batched form: the iterations in as few launches of at most this many as
+  // possible (a NUTS transition counted as 16 evaluations)
+  const int most = std::max(cfg->iters_per_launch, kLaunchEvals / (nuts ? 16 : std::min(a.L, kLaunchEvals)));
+  const int n_launch = (T + most - 1) / most;
+  hipError_t e = for_classes(h, p, s, cap, [&](const ClassRange& c, hipStream_t st) -> hipError_t {
+    hipError_t x = class_spectrum(h, c, data, nullptr, nullptr, st);
+    if (x == hipSuccess && mx) x = class_weights(h, batch, c, st);
     HmcArgs ac = a;
     ac.N = c.N;
     ac.P = c.P;
     ac.gidx = ggidx_ptr(h, p, c);
     ac.n_gal = c.gcount;
     ac.n_steps = 0;
-    hipError_t e = launch_hmc_init(ac, c.gcount, s);
-    if (e != hipSuccess) return hip_fail(h, e, "hmc init launch");
-  }
-  const int T = a.t_stop;
-  if (cfg->form == BSI_FORM_PLAIN) {
-    // one galaxy, one leapfrog step per launch
-    for (const ClassRange& c : p.classes) {
-      for (int i = 0; i < c.gcount; ++i) {
-        HmcArgs ac = a;
-        ac.N = c.N;
-        ac.P = c.P;
-        ac.gidx = ggidx_ptr(h, p, c) + i;
-        ac.n_gal = 1;
-        ac.n_steps = 1;
-        for (int64_t k = 0; k < (int64_t)T * (nuts ? 1 : a.L); ++k) {
-          hipError_t e = launch_hmc_advance(ac, 1, s);
-          if (e != hipSuccess) return hip_fail(h, e, "hmc advance launch");
-        }
-      }
+    if (x == hipSuccess) x = launch_hmc_init(ac, c.gcount, st);
+    if (plain) {
+      // one galaxy, one leapfrog step per launch
+      ac.n_gal = 1;
+      ac.n_steps = 1;
+      for (int i = 0; i < c.gcount; ++i, ++ac.gidx)
+        for (int64_t k = 0; x == hipSuccess && k < (int64_t)T * (nuts ? 1 : a.L); ++k)
+          x = launch_hmc_advance(ac, 1, st);
+      return x;
     }
-  } else {
-    const int ipl = std::min(cfg->iters_per_launch, std::max(T, 1));
-    const int n_launch = (T + ipl - 1) / ipl;
-    auto advance_class = [&](int i, hipStream_t sc) -> hipError_t {
-      const ClassRange& c = p.classes[i];
-      HmcArgs ac = a;
-      ac.N = c.N;
-      ac.P = c.P;
-      ac.wpc = (mx || nuts) ? 1 : hmc_split_waves(c.N, C, c.P, batch->profile, cfg->waves_per_chain);
-      ac.gidx = ggidx_ptr(h, p, c);
-      ac.n_gal = c.gcount;
-      ac.n_steps = nuts ? ipl : ipl * a.L;
-      return launch_hmc_advance(ac, c.gcount, sc);
-    };
-    // direct launches: the sizes run concurrently on forked streams
-    auto enqueue = [&](hipStream_t st) -> hipError_t {
-      return fork_join(h, st, (int)p.classes.size(), advance_class, [&](int i) {
-        const ClassRange& c = p.classes[i];
-        return (double)c.N * c.N * c.gcount;    // the class's share of the work
-      });
-    };
-    // any capture (the library's own graph or the caller's): one stream, the
-    // sizes' launches in sequence.  Capturing the fork/join has ended in a
-    // host segmentation fault inside the call (cause not identified), so it
-    // is never captured.
-    auto enqueue_serial = [&](hipStream_t st) -> hipError_t {
-      for (int i = 0; i < (int)p.classes.size(); ++i) {
-        hipError_t e = advance_class(i, st);
-        if (e != hipSuccess) return e;
-      }
-      return hipSuccess;
-    };
-    if (cap) {
-      // the caller's graph replays this call: its launches go in as they are,
-      // the sizes in sequence on the capturing stream
-      for (int k = 0; k < n_launch; ++k) {
-        hipError_t e = enqueue_serial(s);
-        if (e != hipSuccess) return hip_fail(h, e, "hmc advance launch");
-      }
-    } else if (cfg->use_graph && n_launch > 1) {
-      hipGraph_t graph = nullptr;
-      hipGraphExec_t exec = nullptr;
-      hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed);
-      if (e == hipSuccess) e = enqueue_serial(s);
-      hipError_t e2 = hipStreamEndCapture(s, &graph);
-      if (e == hipSuccess) e = e2;
-      if (e == hipSuccess) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-      for (int k = 0; e == hipSuccess && k < n_launch; ++k) e = hipGraphLaunch(exec, s);
-      if (e != hipSuccess) {
-        // nothing of the graph may still run unless a launch succeeded: wait, then destroy
-        (void)hipStreamSynchronize(s);
-        if (exec) (void)hipGraphExecDestroy(exec);
-        if (graph) (void)hipGraphDestroy(graph);
-        return hip_fail(h, e, "hmc graph");
-      }
-      // the replays are in flight: the graph is destroyed once they have run
-      if ((rc = keep_graph(h, exec, graph, s))) return rc;
-    } else {
-      for (int k = 0; k < n_launch; ++k) {
-        hipError_t e = enqueue(s);
-        if (e != hipSuccess) return hip_fail(h, e, "hmc advance launch");
-      }
+    ac.wpc = (mx || nuts) ? 1 : hmc_split_waves(c.N, C, c.P, batch->profile, cfg->waves_per_chain);
+    for (int k = 0; x == hipSuccess && k < n_launch; ++k) {
+      // evenly sized launches: iterations [k T / n, (k + 1) T / n)
+      const int it = (int)((int64_t)(k + 1) * T / n_launch - (int64_t)k * T / n_launch);
+      ac.n_steps = nuts ? it : it * a.L;
+      x = launch_hmc_advance(ac, c.gcount, st);
     }
-  }
-  hipError_t e = launch_hmc_finalize(static_cast<const ChainState*>(h->state.p), batch->n_gal, C,
-                                     cfg->n_samples, chain_stats, status, s);
+    return x;
+  });
+  if (e != hipSuccess) return hip_fail(h, e, "hmc launch");
+  e = launch_hmc_finalize(static_cast<const ChainState*>(h->state.p), batch->n_gal, C, cfg->n_samples,
+                          chain_stats, status, s);
   if (e != hipSuccess) return hip_fail(h, e, "hmc finalize launch");
   if ((rc = finish(h, s, cap))) return rc;
   if (!stream) {
