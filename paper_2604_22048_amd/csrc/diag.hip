@@ -6,7 +6,8 @@
 // parameter.  The chains pass through LDS one after another as they lie in
 // memory, [S][P], the next one's transfer (straight into LDS) under the
 // current one's arithmetic.  Of a chain, lane l of the parameter's wave takes
-// draws 17 l .. 17 l + 16 (mod 1,088) and the 15 after them as centred float64
+// draws 17 l .. 17 l + 16 (mod 1,088; fewer for short chains) and the 15 after
+// them as centred float64
 // registers and adds the products at 16 lags at once, 272 multiply-adds for
 // 32 LDS reads, into sums that run over the chains; the mean is the only
 // thing needed per chain beforehand.  (17 draws: with six parameters the
@@ -17,7 +18,7 @@
 // Bound by vector issue (half of it busy: 5,000 instructions per series, of
 // which 1,088 are the products; two workgroups of six waves per compute
 // unit).  10,000 galaxies x 4 chains x 1,000 draws x 6 parameters (960 MB):
-// 980 us with split R-hat, 810 without; one workgroup per galaxy and
+// 990 us with split R-hat, 820 without; one workgroup per galaxy and
 // parameter with its draws read at stride P, 64 lags at least and two LDS
 // reads per product took 4,540 us with it.
 #include <algorithm>
@@ -32,16 +33,21 @@ namespace bsi {
 namespace {
 
 constexpr int kLags = 16;          // lags per pass over the chains
-constexpr int kRun = 17;           // consecutive draws per lane
+constexpr int kMaxRun = 17;        // consecutive draws per lane at most
 constexpr int kMaxPar = 8;         // parameters (waves) per workgroup
+constexpr int kMaxParts = 8;       // waves per parameter
 constexpr int kEssChains = 16;     // chains at most
+// Series up to which a series' chains are shared by several waves, one parameter
+// per workgroup: with fewer waves than the chip holds, the latency of a
+// wave's chains one after another counts, not the reads at stride P.
+constexpr int64_t kFewSeries = 3072;
 constexpr size_t kEssLds = 150 * 1024;   // (ess_buf(S, 1) of the longest chains the entry point takes fits)
 constexpr int kWaitVmcnt0 = 0x0F70;   // every vector memory operation done (gfx9 wait counter)
 
 // LDS floats of a chain of S draws at q floats each: the lanes read up to a
 // window past the last draw (masked), the transfer writes up to a wave.
 __host__ __device__ constexpr int ess_buf(int S, int q) {
-  const int tail = (kRun + kLags) * q;
+  const int tail = (kMaxRun + kLags) * q;
   return (S * q + (tail > kWave ? tail : kWave) + 3) & ~3;
 }
 
@@ -75,32 +81,36 @@ __device__ __forceinline__ double var_plus(double W, const double* mean, int M, 
 }
 
 // q parameters per workgroup, q floats per draw in LDS (q = P: a chain as it
-// lies in memory); two buffers, or one.
-template <int q>
-__global__ void __launch_bounds__(kWave* q, q > 4 ? 4 : 2)
-    ess_kernel(int C, int S, int P, int buffers, double tau_min, const float* __restrict__ x,
+// lies in memory); two buffers, or one.  parts > 1: the chains are shared by
+// so many waves per parameter, wave (part j, parameter w) taking chains j,
+// j + parts, ... through buffers of its part's own.
+template <int q, int kRun>
+__global__ void __launch_bounds__(q > 1 ? kWave * q : kWave * kMaxParts, q > 4 ? 4 : 2)
+    ess_kernel(int C, int S, int P, int nparts, int buffers, double tau_min, const float* __restrict__ x,
                float* __restrict__ ess, float* __restrict__ rhat, float* __restrict__ rsplit) {
   extern __shared__ float4 ess_lds4[];
   __shared__ double mean_s[q][kEssChains], half_s[q][2 * kEssChains];
+  __shared__ double part_s[kMaxParts][kLags + 1];      // parts > 1 (q = 1): each part's sums
   float* lds = reinterpret_cast<float*>(ess_lds4);
   const int groups = (P + q - 1) / q;
   const int gal = blockIdx.x / groups, p0 = (blockIdx.x - gal * groups) * q;
-  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int w = q == 1 ? 0 : wave, part = q == 1 ? wave : 0, parts = q == 1 ? nparts : 1;
   const int size = ess_buf(S, q);
   const float* src = x + (int64_t)gal * C * S * P;
-  // start chain c's transfer into its buffer
-  auto fetch = [&](int c) {
-    float* dst = lds + (buffers == 2 && (c & 1) ? size : 0);
+  const int rounds = (C + parts - 1) / parts;
+  auto buffer = [&](int r) { return lds + (part * buffers + (buffers == 2 ? r & 1 : 0)) * size; };
+  // start the transfer of this part's chain of round r
+  auto fetch = [&](int r) {
+    const int c = r * parts + part;
+    if (c >= C) return;
+    float* dst = buffer(r);
     const float* sc = src + (int64_t)c * S * P;
-    if (q == P) {
-      const int n = S * P;
-      for (int i = w * kWave; i < n; i += blockDim.x)
-        __builtin_amdgcn_global_load_lds(sc + min(i + lane, n - 1), dst + i, 4, 0, 0);
-    } else {
-      for (int i = threadIdx.x; i < S * q; i += blockDim.x) {
-        const int s = i / q, p = p0 + (i - s * q);
-        dst[i] = sc[(int64_t)s * P + min(p, P - 1)];
-      }
+    const int n = S * q;
+    for (int i = w * kWave; i < n; i += q * kWave) {
+      const int k = min(i + lane, n - 1);
+      const int64_t o = q == P ? k : (int64_t)(k / q) * P + min(p0 + k % q, P - 1);
+      __builtin_amdgcn_global_load_lds(sc + o, dst + i, 4, 0, 0);
     }
   };
   const int h = S / 2;
@@ -156,16 +166,17 @@ __global__ void __launch_bounds__(kWave* q, q > 4 ? 4 : 2)
     for (int t = 0; t < kLags; ++t) acc[t] = 0.0;
     if (buffers == 2) fetch(0);
 #pragma clang loop unroll(disable)
-    for (int c = 0; c < C; ++c) {
+    for (int r = 0; r < rounds; ++r) {
       if (buffers == 1) {
         __syncthreads();     // the last chain has been read
-        fetch(c);
+        fetch(r);
       }
       __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-      __syncthreads();       // chain c is there, and the other buffer has been read
-      if (buffers == 2 && c + 1 < C) fetch(c + 1);
-      if (done) continue;
-      const float* col = lds + (buffers == 2 && (c & 1) ? size : 0) + w;
+      __syncthreads();       // this round's chains are there, and the other buffers have been read
+      if (buffers == 2 && r + 1 < rounds) fetch(r + 1);
+      const int c = r * parts + part;
+      if (done || c >= C) continue;
+      const float* col = buffer(r) + w;
       if (FIRST) moments(c, col);
       const double mean = mean_s[w][c];
       // runs whose every product is past the chain's end are skipped
@@ -189,8 +200,23 @@ __global__ void __launch_bounds__(kWave* q, q > 4 ? 4 : 2)
         }
       }
     }
+    if (done && parts == 1) return;
+    double tot = wave_total16(acc);      // lag 16 m + lane / 4
+    if (parts > 1) {
+      // every part's wave adds the parts' sums in their order and goes on alike
+      const double mine = FIRST && rsplit ? wave_total(q2) : 0.0;
+      if ((lane & 3) == 0) part_s[part][lane >> 2] = tot;
+      if (lane == 1) part_s[part][kLags] = mine;
+      __syncthreads();
+      tot = 0.0;
+      q2 = 0.0;
+      for (int j = 0; j < parts; ++j) {
+        tot += part_s[j][lane >> 2];
+        if (lane == 0) q2 += part_s[j][kLags];
+      }
+      __syncthreads();
+    }
     if (done) return;
-    const double tot = wave_total16(acc);      // lag 16 m + lane / 4
     if (FIRST) {
       W = bcast(tot, 0) / ((S - 1.0) * C);
       vp = var_plus(W, mean_s[w], C, S);
@@ -200,7 +226,7 @@ __global__ void __launch_bounds__(kWave* q, q > 4 ? 4 : 2)
         v2 = var_plus(w2, half_s[w], 2 * C, h);
       }
       // R-hat on lane 0, split R-hat on lane 1
-      float* o = lane == 0 ? rhat : lane == 1 ? rsplit : nullptr;
+      float* o = part > 0 ? nullptr : lane == 0 ? rhat : lane == 1 ? rsplit : nullptr;
       if (o) o[(int64_t)gal * P + p0 + w] = (float)sqrt(lane == 0 ? vp / W : v2 / w2);
       done = !(vp > 0.0);
     }
@@ -217,7 +243,7 @@ __global__ void __launch_bounds__(kWave* q, q > 4 ? 4 : 2)
       }
     }
     if (kLags * (m + 1) >= S) done = true;
-    if (done && ess && lane == 0) {
+    if (done && ess && part == 0 && lane == 0) {
       const double n = (double)C * S;
       double tau = (vp > 0.0 && tau_sum > 0.0) ? -1.0 + 2.0 * tau_sum : 1.0;
       tau = fmax(tau, tau_min);
@@ -238,24 +264,38 @@ hipError_t launch_ess(int n_gal, int C, int S, int P, const float* samples, floa
   // the parameters (at most 8) whose draws of one chain fit LDS; a second
   // buffer where two workgroups of them still fit a compute unit (1,600 draws
   // of six parameters)
-  int q = std::min(P, kMaxPar);
+  int q = std::min(P, kMaxPar), parts = 1;
   while (q > 1 && sizeof(float) * (size_t)ess_buf(S, q) > kEssLds) --q;
-  const size_t buf = sizeof(float) * (size_t)ess_buf(S, q);
+  if ((int64_t)n_gal * P <= kFewSeries && C > 1) {
+    q = 1;
+    parts = std::min(C, kMaxParts);
+    while (parts > 1 && parts * sizeof(float) * (size_t)ess_buf(S, 1) > kEssLds) --parts;
+  }
+  const size_t buf = parts * sizeof(float) * (size_t)ess_buf(S, q);
   const int buffers = buf <= 40 * 1024 ? 2 : 1;
   auto go = [&](auto kern) {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(buffers * buf));
-    hipLaunchKernelGGL(kern, dim3(n_gal * ((P + q - 1) / q)), dim3(kWave * q), buffers * buf, s, C, S, P, buffers,
-                       1.0 / std::log10((double)C * S), samples, ess, rhat, rsplit);
+    hipLaunchKernelGGL(kern, dim3(n_gal * ((P + q - 1) / q)), dim3(kWave * q * parts), buffers * buf, s, C, S, P,
+                       parts, buffers, 1.0 / std::log10((double)C * S), samples, ess, rhat, rsplit);
+  };
+  // the shortest run with which one round of the wave's lanes takes a chain
+  // (a wave's time goes with the run, not with the draws); odd, so that the
+  // lanes' LDS reads fall on different banks
+  auto run = [&](auto qc) {
+    constexpr int Q = decltype(qc)::value;
+    if (S <= 5 * kWave) go(ess_kernel<Q, 5>);
+    else if (S <= 9 * kWave) go(ess_kernel<Q, 9>);
+    else go(ess_kernel<Q, kMaxRun>);
   };
   switch (q) {
-    case 1: go(ess_kernel<1>); break;
-    case 2: go(ess_kernel<2>); break;
-    case 3: go(ess_kernel<3>); break;
-    case 4: go(ess_kernel<4>); break;
-    case 5: go(ess_kernel<5>); break;
-    case 6: go(ess_kernel<6>); break;
-    case 7: go(ess_kernel<7>); break;
-    default: go(ess_kernel<8>); break;
+    case 1: run(std::integral_constant<int, 1>()); break;
+    case 2: run(std::integral_constant<int, 2>()); break;
+    case 3: run(std::integral_constant<int, 3>()); break;
+    case 4: run(std::integral_constant<int, 4>()); break;
+    case 5: run(std::integral_constant<int, 5>()); break;
+    case 6: run(std::integral_constant<int, 6>()); break;
+    case 7: run(std::integral_constant<int, 7>()); break;
+    default: run(std::integral_constant<int, 8>()); break;
   }
   return hipGetLastError();
 }

@@ -1,5 +1,6 @@
-"""bsi_ess at the edges of its layout: blocks of 16 draws, 1,024 draws per wave
-pass, 16 lags per pass over the chains, parameters per workgroup."""
+"""bsi_ess at the edges of its layout: runs of 5, 9 and 17 draws per lane, 64 runs
+per wave round, 16 lags per pass over the chains, parameters per workgroup, and
+the chains shared by several waves up to 3,072 series."""
 import numpy as np
 import pytest
 
@@ -16,7 +17,9 @@ def bsi(device):
 
 # (galaxies, chains, draws, parameters, memory of the chains in draws)
 SHAPES = [(3, 1, 4, 1, 0), (2, 16, 15, 6, 0), (2, 2, 16, 5, 1), (3, 4, 17, 9, 2), (1, 4, 1024, 6, 3),
-          (2, 2, 1041, 7, 40), (1, 3, 2500, 6, 200), (1, 1, 18944, 2, 30)]
+          (2, 2, 1041, 7, 40), (1, 3, 2500, 6, 200), (1, 1, 18944, 2, 30),
+          (1, 11, 321, 3, 0), (3100, 2, 33, 1, 1), (1600, 1, 320, 2, 0), (800, 3, 577, 4, 2), (400, 2, 90, 8, 30),
+          (400, 2, 600, 9, 0), (700, 2, 1089, 5, 4)]
 
 
 @pytest.mark.parametrize("G,C,S,P,memory", SHAPES)
@@ -36,7 +39,7 @@ def test_ess_layout_edges(bsi, G, C, S, P, memory):
     e2 = bsi.ess(torch.tensor(x).cuda())[0].cpu().numpy()
     assert np.array_equal(e2, e.astype(np.float32))
     tol = 2.0 ** -23
-    for g in range(G):
+    for g in sorted({0, G // 2, G - 1}):
         for p in range(P):
             y = x[g, :, :, p].astype(np.float64)
             assert abs(e[g, p] / diagnostics.ess(y) - 1) < tol
