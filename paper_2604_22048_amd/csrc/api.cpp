@@ -38,6 +38,7 @@ struct ClassRange {
 
 struct Plan {
   int E = 1;                      // exposures per galaxy
+  bool packed = false;            // one stamp side, stamp i at i N^2: no index lists (NULL to the kernels)
   std::vector<int32_t> gidx;      // stamps grouped by stamp side (a galaxy's exposures in order)
   std::vector<int32_t> ggidx;     // galaxies grouped by stamp side
   std::vector<int64_t> bin_off;   // per stamp, offset into the bin buffer (complex units)
@@ -83,10 +84,26 @@ int plan_of(bsi_handle h, int N) {
   return P > 0 ? P : make_slot_plan(N).P;
 }
 
-Plan make_plan(bsi_handle h, const bsi_batch* b) {
+// Whether every stamp has one side and they lie packed from the start.
+bool packed_batch(const bsi_batch* b) {
+  const int64_t n = (int64_t)b->n_gal * exposures(b), N = b->n[0];
+  for (int64_t i = 0; i < n; ++i)
+    if (b->n[i] != N || b->off[i] != i * N * N) return false;
+  return true;
+}
+
+// may_pack: the call's kernels take a packed batch without index lists.
+Plan make_plan(bsi_handle h, const bsi_batch* b, bool may_pack = false) {
   Plan p;
   p.E = exposures(b);
   const int E = p.E;
+  if (may_pack && packed_batch(b)) {
+    const int n = b->n_gal * E, N = b->n[0];
+    p.packed = true;
+    p.classes.push_back({N, plan_of(h, N), 0, n, 0, b->n_gal});
+    p.max_pixel = (int64_t)n * N * N;
+    return p;
+  }
   std::map<int, std::vector<int32_t>> by;
   for (int i = 0; i < b->n_gal; ++i) by[b->n[(int64_t)i * E]].push_back(i);
   p.bin_off.assign((size_t)b->n_gal * E, 0);
@@ -119,6 +136,7 @@ struct PlanBytes {
 };
 
 PlanBytes plan_bytes(const bsi_batch* b, const Plan& p) {
+  if (p.packed) return {0, 0, 0, 0};
   const size_t n = (size_t)b->n_gal * p.E;     // stamps
   return {n * sizeof(int32_t), n * sizeof(int64_t), n * sizeof(int64_t),
           p.E > 1 ? (size_t)b->n_gal * sizeof(int32_t) : 0};
@@ -134,18 +152,18 @@ int upload_plan(bsi_handle h, const bsi_batch* b, const Plan& p, hipStream_t s, 
 }
 
 // The class's stamps, and its galaxies (the same list when E = 1).
-const int32_t* gidx_ptr(bsi_handle h, const ClassRange& c) {
-  return static_cast<const int32_t*>(h->gidx.p) + c.begin;
+const int32_t* gidx_ptr(bsi_handle h, const Plan& p, const ClassRange& c) {
+  return p.packed ? nullptr : static_cast<const int32_t*>(h->gidx.p) + c.begin;
 }
 
 const int32_t* ggidx_ptr(bsi_handle h, const Plan& p, const ClassRange& c) {
-  return static_cast<const int32_t*>(p.E > 1 ? h->ggidx.p : h->gidx.p) + c.gbegin;
+  return p.packed ? nullptr : static_cast<const int32_t*>(p.E > 1 ? h->ggidx.p : h->gidx.p) + c.gbegin;
 }
 
 // Per-bin noise weights (sqrt w beside the spectrum, which is whitened) of one
 // size class of a batch with several exposures or correlated noise.
-hipError_t class_weights(bsi_handle h, const bsi_batch* b, const ClassRange& c, hipStream_t s) {
-  return launch_whiten(b->noise_ps, gidx_ptr(h, c), c.count, static_cast<const int64_t*>(h->off.p),
+hipError_t class_weights(bsi_handle h, const bsi_batch* b, const Plan& p, const ClassRange& c, hipStream_t s) {
+  return launch_whiten(b->noise_ps, gidx_ptr(h, p, c), c.count, static_cast<const int64_t*>(h->off.p),
                        static_cast<const int64_t*>(h->bin_off.p), c.N, c.P, static_cast<float2*>(h->dh.p),
                        static_cast<float*>(h->sqw.p), s);
 }
@@ -153,9 +171,9 @@ hipError_t class_weights(bsi_handle h, const bsi_batch* b, const ClassRange& c, 
 inline bool weighted(const bsi_batch* b) { return b->n_exp > 1 || b->noise_ps != nullptr; }
 
 // The data spectra (model: of data - model, with its chi2) of one size class.
-hipError_t class_spectrum(bsi_handle h, const ClassRange& c, const float* data, const double* model,
+hipError_t class_spectrum(bsi_handle h, const Plan& p, const ClassRange& c, const float* data, const double* model,
                           double* chi2, hipStream_t s) {
-  return launch_stamp_dft(transform_of(h, c.N) == BSI_TRANSFORM_MFMA, data, model, gidx_ptr(h, c), c.count,
+  return launch_stamp_dft(transform_of(h, c.N) == BSI_TRANSFORM_MFMA, data, model, gidx_ptr(h, p, c), c.count,
                           static_cast<const int64_t*>(h->off.p), static_cast<const int64_t*>(h->bin_off.p), c.N,
                           c.P, static_cast<float2*>(h->dh.p), chi2, s);
 }
@@ -268,6 +286,11 @@ int bsi_create(bsi_handle* out, int32_t device, const char* tune_cache) {
     g_create_error = "device scratch lookup failed";
     return BSI_EHIP;
   }
+  if (init_dft_tables(device) != hipSuccess) {
+    (void)hipGetLastError();
+    g_create_error = "DFT table initialisation failed";
+    return BSI_EHIP;
+  }
   bsi_ctx* h = new bsi_ctx();
   h->device = device;
   h->num_cu = prop.multiProcessorCount;
@@ -346,7 +369,7 @@ int bsi_render_stamps(bsi_handle h, const bsi_batch* batch, const float* params,
   if ((rc = upload_plan(h, batch, p, s, cap))) return rc;
   const float rs = profile_rscale(batch->profile, batch->pixel_scale, batch->spergel_nu);
   for (const ClassRange& c : p.classes) {
-    const int32_t* gi = gidx_ptr(h, c);
+    const int32_t* gi = gidx_ptr(h, p, c);
     const int64_t* off = static_cast<const int64_t*>(h->off.p);
     hipError_t e = transform_of(h, c.N) == BSI_TRANSFORM_MFMA
         ? launch_render_mfma(params, batch->psf_fwhm, gi, c.count, off, c.N, rs,
@@ -375,48 +398,65 @@ int bsi_loglik_grad(bsi_handle h, const bsi_batch* batch, const float* data, con
   (void)hipSetDevice(h->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool cap = capturing(s);
-  const Plan p = make_plan(h, batch);
-  const PlanBytes pb = plan_bytes(batch, p);
   const bool pixel = method == BSI_LIK_PIXEL;
   const bool mx = weighted(batch);
-  if ((rc = prepare(h, s, cap,
+  // transform and contraction in one kernel, or through spectra in memory
+  auto fused = [&](int N, int stamps) {
+    return transform_of(h, N) == BSI_TRANSFORM_MFMA && loglik_fused(N, plan_of(h, N), mx, stamps);
+  };
+  const Plan p = make_plan(h, batch, !pixel && fused(batch->n[0], batch->n_gal * exposures(batch)));
+  const PlanBytes pb = plan_bytes(batch, p);
+  bool spectra = false;
+  for (const ClassRange& c : p.classes) spectra |= !fused(c.N, c.count);
+  if (!p.packed &&
+      (rc = prepare(h, s, cap,
                     {{&h->gidx, pb.gidx}, {&h->off, pb.off}, {&h->bin_off, pb.bin_off},
-                     {&h->ggidx, pb.ggidx}, {&h->dh, (size_t)p.total_bins * sizeof(float2)},
-                     {&h->sqw, mx ? (size_t)p.total_bins * sizeof(float) : 0},
+                     {&h->ggidx, pb.ggidx}, {&h->dh, spectra ? (size_t)p.total_bins * sizeof(float2) : 0},
+                     {&h->sqw, spectra && mx ? (size_t)p.total_bins * sizeof(float) : 0},
                      {&h->model, pixel ? (size_t)p.max_pixel * sizeof(double) : 0},
-                     {&h->chi2, pixel ? (size_t)batch->n_gal * sizeof(double) : 0}},
+                     {&h->chi2, spectra && pixel ? (size_t)batch->n_gal * sizeof(double) : 0}},
                     pb.stage())))
     return rc;
   if ((rc = upload_plan(h, batch, p, s, cap))) return rc;
-  const float rs = profile_rscale(batch->profile, batch->pixel_scale, batch->spergel_nu);
-  const int64_t* off = static_cast<const int64_t*>(h->off.p);
-  double* chi2 = nullptr;
-  const double* model = nullptr;
-  if (pixel) {
-    for (const ClassRange& c : p.classes) {
-      hipError_t e = launch_render_f64(params, batch->psf_fwhm, gidx_ptr(h, c), c.count, off, c.N,
-                                       rs, 1.0f / batch->pixel_scale, batch->profile, batch->spergel_nu,
-                                       static_cast<double*>(h->model.p), s);
-      if (e != hipSuccess) return hip_fail(h, e, "render launch");
+  LoglikArgs a{};
+  a.off = p.packed ? nullptr : static_cast<const int64_t*>(h->off.p);
+  a.model = pixel ? static_cast<const double*>(h->model.p) : nullptr;
+  a.noise_ps = batch->noise_ps;
+  a.dh = static_cast<const float2*>(h->dh.p);
+  a.bin_off = static_cast<const int64_t*>(h->bin_off.p);
+  a.sqw = static_cast<const float*>(h->sqw.p);
+  a.chi2 = static_cast<const double*>(h->chi2.p);
+  a.params = params;
+  a.psf = batch->psf_fwhm;
+  a.sigma = batch->sigma;
+  a.n_exp = p.E;
+  a.rscale = profile_rscale(batch->profile, batch->pixel_scale, batch->spergel_nu);
+  a.pscale_inv = 1.0f / batch->pixel_scale;
+  a.nu = batch->spergel_nu;
+  a.loglik = loglik;
+  a.grad = grad;
+  a.status = status;
+  hipError_t e = for_classes(h, p, s, cap, [&](const ClassRange& c, hipStream_t st) -> hipError_t {
+    LoglikArgs ac = a;
+    ac.N = c.N;
+    ac.P = c.P;
+    ac.gidx = ggidx_ptr(h, p, c);
+    ac.n = c.gcount;
+    hipError_t x = hipSuccess;
+    if (pixel)
+      x = launch_render_f64(params, batch->psf_fwhm, gidx_ptr(h, p, c), c.count, a.off, c.N, a.rscale, a.pscale_inv,
+                            batch->profile, batch->spergel_nu, static_cast<double*>(h->model.p), st);
+    if (fused(c.N, c.count)) {
+      ac.data = data;
+    } else {
+      if (x == hipSuccess)
+        x = class_spectrum(h, p, c, data, a.model, pixel ? static_cast<double*>(h->chi2.p) : nullptr, st);
+      if (x == hipSuccess && mx) x = class_weights(h, batch, p, c, st);
     }
-    model = static_cast<const double*>(h->model.p);
-    chi2 = static_cast<double*>(h->chi2.p);
-  }
-  for (const ClassRange& c : p.classes) {
-    hipError_t e = class_spectrum(h, c, data, model, chi2, s);
-    if (e == hipSuccess && mx) e = class_weights(h, batch, c, s);
-    if (e != hipSuccess) return hip_fail(h, e, "data spectrum launch");
-  }
-  for (const ClassRange& c : p.classes) {
-    hipError_t e = launch_loglik(static_cast<const float2*>(h->dh.p),
-                                 static_cast<const int64_t*>(h->bin_off.p), ggidx_ptr(h, p, c),
-                                 c.gcount, params, batch->psf_fwhm, batch->sigma, c.N, c.P, rs,
-                                 1.0f / batch->pixel_scale, batch->profile, batch->spergel_nu,
-                                 method == BSI_LIK_PIXEL, chi2, loglik, grad, status, s, p.E,
-                                 mx ? static_cast<const float*>(h->sqw.p) : nullptr);
-    if (e != hipSuccess) return hip_fail(h, e, "loglik launch");
-  }
-  return finish(h, s, cap);
+    return x == hipSuccess ? launch_loglik(ac, batch->profile, pixel, mx, st) : x;
+  });
+  if (e != hipSuccess) return hip_fail(h, e, "loglik launch");
+  return p.packed ? BSI_OK : finish(h, s, cap);    // packed: no workspace used
 }
 
 int bsi_hmc_sample(bsi_handle h, const bsi_batch* batch, const float* data, const float* ref_xy,
@@ -533,8 +573,8 @@ int bsi_hmc_sample(bsi_handle h, const bsi_batch* batch, const float* data, cons
   const int most = std::max(cfg->iters_per_launch, kLaunchEvals / (nuts ? 16 : std::min(a.L, kLaunchEvals)));
   const int n_launch = (T + most - 1) / most;
   hipError_t e = for_classes(h, p, s, cap, [&](const ClassRange& c, hipStream_t st) -> hipError_t {
-    hipError_t x = class_spectrum(h, c, data, nullptr, nullptr, st);
-    if (x == hipSuccess && mx) x = class_weights(h, batch, c, st);
+    hipError_t x = class_spectrum(h, p, c, data, nullptr, nullptr, st);
+    if (x == hipSuccess && mx) x = class_weights(h, batch, p, c, st);
     HmcArgs ac = a;
     ac.N = c.N;
     ac.P = c.P;

@@ -28,7 +28,15 @@ inline float profile_rscale(int prof, float pixel_scale, float nu = 0.5f) {
 size_t dft_bins_lds_bytes(int N);
 size_t render_lds_bytes(int N);
 size_t render_mfma_lds_bytes(int N);
-size_t dft_bins_mfma_lds_bytes(int N);
+size_t dft_bins_mfma_lds_bytes(int N, int P);
+// DFT operand and PSF-sinc tables of one stamp side (dft_device.h), the current
+// device's: filled by init_dft_tables, once per device.
+struct DftTab {
+  const float2* dft;
+  const double2* sinc;      // {k_u, sinc(u / N)}, u = 0..N / 2
+};
+DftTab dft_tables(int N);
+hipError_t init_dft_tables(int device);
 // The transforms as FP32 DFT products on the matrix cores (dft_mfma.hip)
 hipError_t launch_render_mfma(const float* params, const float* psf, const int32_t* gidx, int n,
                               const int64_t* off, int N, float rscale, float pscale_inv, int prof, float nu,
@@ -58,11 +66,35 @@ hipError_t launch_whiten(const float* noise_ps, const int32_t* gidx, int n, cons
                          const int64_t* bin_off, int N, int P, float2* dh, float* sqw, hipStream_t s);
 
 // ---- likelihood.hip ----
-hipError_t launch_loglik(const float2* dh, const int64_t* bin_off, const int32_t* gidx, int n,
-                         const float* params, const float* psf, const float* sigma, int N, int P,
-                         float rscale, float pscale_inv, int prof, float nu, int resid_mode,
-                         const double* chi2_pix, double* loglik, float* grad, uint32_t* status,
-                         hipStream_t s, int n_exp = 1, const float* sqw = nullptr);
+struct LoglikArgs {
+  // the stamps (transformed in the kernel), model (RESID: float64 model stamps
+  // at the same offsets), offsets (NULL: stamp i at i N^2) and noise powers
+  // (MX; NULL: white); or, data NULL, the spectra at dh + bin_off with sqrt w
+  // at sqw + bin_off (MX) and sum (data - model)^2 in chi2 (RESID)
+  const float* data;
+  const double* model;
+  const int64_t* off;
+  const float* noise_ps;
+  const float2* dh;
+  const int64_t* bin_off;
+  const float* sqw;
+  const double* chi2;
+  const int32_t* gidx;      // the launch's n galaxies (NULL: 0..n-1)
+  int n;
+  const float* params;
+  const float* psf;
+  const float* sigma;
+  int N, P, n_exp;
+  float rscale, pscale_inv, nu;
+  DftTab tab;               // set by the launch
+  double* loglik;
+  float* grad;
+  uint32_t* status;
+};
+// Whether a class of so many stamps of side N is transformed and contracted in
+// one kernel (LoglikArgs::data) rather than in two.
+bool loglik_fused(int N, int P, bool mx, int stamps);
+hipError_t launch_loglik(LoglikArgs a, int prof, bool resid, bool mx, hipStream_t s);
 
 // ---- hmc.hip ----
 // Per-chain device state: 64 words, loaded and stored one word per lane.
@@ -281,7 +313,7 @@ inline hipError_t launch_stamp_dft(bool mfma, const float* data, const double* m
                                    const int32_t* gidx, int n, const int64_t* off,
                                    const int64_t* bin_off, int N, int P, float2* out, double* chi2,
                                    hipStream_t s) {
-  if (mfma && dft_bins_mfma_lds_bytes(N) <= 160 * 1024)
+  if (mfma && dft_bins_mfma_lds_bytes(N, P) <= 160 * 1024 - 64)
     return launch_dft_bins_mfma(data, model, gidx, n, off, bin_off, N, P, out, chi2, s);
   return launch_dft_bins(data, model, gidx, n, off, bin_off, N, P, out, chi2, nullptr, s);
 }

@@ -28,6 +28,8 @@
 #include <string>
 #include <vector>
 
+#include "stage.h"
+
 struct DevBuf {
   void* p = nullptr;
   size_t n = 0;
@@ -248,35 +250,37 @@ int save_tune_cache(bsi_handle h);
 
 }  // namespace bsi_host
 
-namespace bsi {
-// stage.hip: copy n 16-byte words from mapped host memory to device memory.
-hipError_t launch_stage_copy(const void* src_dev, void* dst, size_t bytes, hipStream_t s);
-}  // namespace bsi
-
 namespace bsi_host {
 
 // Copy host pieces to device workspace through the staging buffer: wait for
 // the previous reader of the staging buffer, pack, and enqueue one copy
-// kernel per piece (kernel nodes only, so the call can be captured; a
-// captured graph reads the staging buffer at each replay).
+// kernel (a kernel node, so the call can be captured; a captured graph reads
+// the staging buffer at each replay).  Nothing is done for no bytes.
 inline int stage_upload(bsi_handle h, hipStream_t s, bool cap, std::initializer_list<Piece> pieces) {
   size_t total = 0;
   for (const Piece& p : pieces) total += (p.bytes + 15) & ~size_t(15);
-  if (total > h->stage_n) return fail(h, BSI_EINVAL, "staging buffer too small (internal)");
+  if (total == 0) return BSI_OK;
+  if (total > h->stage_n || pieces.size() > (size_t)bsi::kStagePieces)
+    return fail(h, BSI_EINVAL, "staging buffer too small (internal)");
   if (h->stage_pending) {
     hipError_t e = hipEventSynchronize(h->ev_stage);
     if (e != hipSuccess) return hip_fail(h, e, "staging reuse");
     h->stage_pending = false;
   }
+  bsi::StagePieces sp{};
   size_t o = 0;
   for (const Piece& p : pieces) {
-    if (p.bytes) std::memcpy(static_cast<char*>(h->stage) + o, p.src, p.bytes);
-    hipError_t e = bsi::launch_stage_copy(static_cast<const char*>(h->stage_dev) + o, p.dst, p.bytes, s);
-    if (e != hipSuccess) return hip_fail(h, e, "staging copy");
+    if (!p.bytes) continue;
+    std::memcpy(static_cast<char*>(h->stage) + o, p.src, p.bytes);
+    sp.src[sp.n] = static_cast<const char*>(h->stage_dev) + o;
+    sp.dst[sp.n] = p.dst;
+    sp.bytes[sp.n++] = p.bytes;
     o += (p.bytes + 15) & ~size_t(15);
   }
+  hipError_t e = bsi::launch_stage_copy(sp, s);
+  if (e != hipSuccess) return hip_fail(h, e, "staging copy");
   if (!cap) {
-    hipError_t e = hipEventRecord(h->ev_stage, s);
+    e = hipEventRecord(h->ev_stage, s);
     if (e != hipSuccess) return hip_fail(h, e, "staging event");
     h->stage_pending = true;
   }

@@ -13,24 +13,49 @@
 // weights) are formed in float64 and rounded; G(q) and the products are
 // float32.
 //
-// dft_bins_mfma_kernel -- the forward DFT of a stamp (or of data - model)
-// at the half-plane bins of the k-space likelihood, written in slot order:
-//   pass A  Q[v][x] = sum_y d[y][x] e^{-i k_v y'}      (rows v = 0..h; -h for
-//                                                       the last row of even N)
-//   pass B  D[v][u] = sum_x Q[v][x] e^{-i k_u x'}      (the N DFT columns u)
-#include "bsi_kernels.h"
-#include "kspace.h"
-
+// dft_bins_mfma_kernel -- the forward DFT of a stamp (or of data - model) at the
+// half-plane bins of the k-space likelihood, written in slot order
+// (dft_device.h).
 #include <algorithm>
+#include <array>
+#include <mutex>
+
+#include "bsi_kernels.h"
+#include "dft_device.h"
 
 namespace bsi {
 
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+// ---- tables ------------------------------------------------------------------
 
-__device__ __forceinline__ f32x4 mfma16x16x4(float a, float b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+constexpr int kDftTabLen = dft_tab_off(kMaxN + 1);
+__device__ __align__(16) float2 dft_tab[kDftTabLen + kAhead * 64];       // 4 MB
+__device__ double2 sinc_tab[(kMaxN + 1) * kSincLen];
+
+// One block per stamp side from 8: the side's operands and {k_u, sinc} pairs.
+__global__ void __launch_bounds__(256) dft_tables_kernel() {
+  const int N = 8 + blockIdx.x;
+  const DftDims d = dft_dims(N);
+  float2* tab = dft_tab + dft_tab_off(N);
+  for (int t = threadIdx.x; t < d.nblk * d.steps * 64; t += blockDim.x) {
+    const int lane = t & 63, s = (t >> 6) % d.steps, blk = (t >> 6) / d.steps;
+    const int li = lane & 15, pix = 4 * s + (lane >> 4);
+    const bool merged = blk == d.nrb;
+    const int f = merged ? 16 * (d.nrb - 1) + (li & 7) : 16 * blk + li;
+    float2 w = make_float2(0.f, 0.f);
+    if (pix < N && f <= d.h) {
+      const bool neg = (merged && li >= 8) || ((N & 1) == 0 && f == d.h);   // (Nyquist: -h)
+      double sn, c;
+      sincospi((double)tw_index(neg ? -f : f, pix, N) / (double)N, &sn, &c);
+      w = make_float2((float)c, (float)(-sn));
+    }
+    tab[t] = w;
+  }
+  for (int u = threadIdx.x; u <= d.h; u += blockDim.x)
+    sinc_tab[N * kSincLen + u] =
+        make_double2(2.0 * 3.14159265358979323846 * u / N,
+                     u == 0 ? 1.0 : sinpi((double)u / N) / (3.14159265358979323846 * u / N));
 }
 
 struct RenderDims {
@@ -198,150 +223,113 @@ __global__ void __launch_bounds__(256) render_mfma_kernel(
   }
 }
 
-// LDS of the forward transform: region 1 holds the stamp (float, N x N) and
-// then D (float2, nrow x N); region 2 holds Q (float2, nrow x ldK), ldK = N
-// rounded up to 4; twiddles after them.
-__host__ __device__ inline size_t dft_mfma_lds(int N) {
-  const int nrow = N / 2 + 1, ldK = (N + 3) & ~3;
-  const size_t r1 = std::max<size_t>((size_t)N * N * sizeof(float), (size_t)nrow * N * sizeof(float2));
-  return ((r1 + 15) & ~(size_t)15) + sizeof(float2) * ((size_t)nrow * ldK + 2 * N);
+// U units per wave (dft_per_wave); with four (dft_big) the DFT table is read from
+// memory instead of LDS.  Bound by the matrix cores, 55 % busy: the stamp's way
+// in and the spectrum's way out are under other workgroups' products (5 per
+// compute unit at 53 px).  10,000 stamps of 53 px: 150 us (218 with the factors
+// from a 2N-entry table, one stamp per workgroup).
+template <int U>
+__global__ void __launch_bounds__(512, U == 1 ? 5 : U == 2 ? 4 : 2) dft_bins_mfma_kernel(
+    const float* __restrict__ data, const double* __restrict__ model, const int32_t* __restrict__ gidx, int n,
+    const int64_t* __restrict__ off, const int64_t* __restrict__ bin_off, int N, int P,
+    const float2* __restrict__ tab, float2* __restrict__ out, double* __restrict__ chi2) {
+  constexpr bool BIG = U > 2;
+  extern __shared__ float4 smd4[];
+  __shared__ double red[8];
+  const SlotPlan sp = make_slot_plan_p(N, P);
+  const DftLds l = dft_lds(N, sp);
+  char* base = reinterpret_cast<char*>(smd4);
+  float* R = reinterpret_cast<float*>(base);
+  int* rows = reinterpret_cast<int*>(base + l.r);
+  float2* t = reinterpret_cast<float2*>(base + l.r + l.rows);
+  if (!BIG) load_table(N, tab, t);
+  dft_row_bases(N, sp, rows);
+  for (int i = blockIdx.x; i < n; i += gridDim.x) {
+    const int gal = gidx[i];
+    const int64_t o = off[gal];
+    double sq = load_stamp(N, data + o, model ? model + o : nullptr, R);
+    if (chi2) {
+      sq = wave_sum(sq);
+      if (lane_id() == 0) red[threadIdx.x / kWave] = sq;
+    }
+    __syncthreads();
+    if (chi2 && threadIdx.x == 0) {
+      double tot = 0.0;
+      for (int w = 0; w < (int)(blockDim.x / kWave); ++w) tot += red[w];
+      chi2[gal] = tot;
+    }
+    const float next = i + gridDim.x < n ? touch_stamp(N, data + off[gidx[i + gridDim.x]]) : 0.f;
+    stamp_dft<U, false>(N, sp, BIG ? tab : t, R, rows, nullptr, nullptr);
+    touch_done(next);
+    __syncthreads();
+    // nbins is even, and so is every spectrum's offset
+    float4* dst = reinterpret_cast<float4*>(out + bin_off[gal]);
+    const float4* src = reinterpret_cast<const float4*>(R);
+    for (int b = threadIdx.x; b < sp.nbins / 2; b += blockDim.x) dst[b] = src[b];
+    __syncthreads();
+  }
 }
 
-__global__ void __launch_bounds__(256) dft_bins_mfma_kernel(
-    const float* __restrict__ data, const double* __restrict__ model, const int32_t* __restrict__ gidx,
-    const int64_t* __restrict__ off, const int64_t* __restrict__ bin_off, int N, int P,
-    float2* __restrict__ out, double* __restrict__ chi2) {
-  extern __shared__ float4 smd4[];
-  __shared__ double red[4];
-  const int h = N / 2, nrow = h + 1, ldK = (N + 3) & ~3, Np = (N + 15) & ~15;
-  const bool even = (N & 1) == 0;
-  const size_t r1 = std::max<size_t>((size_t)N * N * sizeof(float), (size_t)nrow * N * sizeof(float2));
-  char* base = reinterpret_cast<char*>(smd4);
-  float* d = reinterpret_cast<float*>(base);                           // region 1: stamp
-  float2* D = reinterpret_cast<float2*>(base);                         // region 1: spectrum
-  float2* Q = reinterpret_cast<float2*>(base + ((r1 + 15) & ~(size_t)15));
-  float2* tw = Q + nrow * ldK;
-  const int gal = gidx[blockIdx.x];
-  const int64_t o = off[gal];
-  double sq = 0.0;
-  for (int t = threadIdx.x; t < N * N; t += blockDim.x) {
-    double x = (double)data[o + t];
-    if (model) x -= model[o + t];
-    d[t] = (float)x;
-    sq += x * x;
-  }
-  for (int m = threadIdx.x; m < 2 * N; m += blockDim.x) {
-    double s, c;
-    sincospi((double)m / (double)N, &s, &c);
-    tw[m] = make_float2((float)c, (float)(-s));
-  }
-  if (chi2) {
-    sq = wave_sum(sq);
-    if (lane_id() == 0) red[threadIdx.x / kWave] = sq;
-  }
-  __syncthreads();
-  if (chi2 && threadIdx.x == 0) chi2[gal] = red[0] + red[1] + red[2] + red[3];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  const int nrb = (nrow + 15) >> 4, ncb = Np >> 4;
-  // pass A: tiles of Q (16 rows v x 16 columns x), K = y
-  for (int ti = wave; ti < nrb * ncb; ti += 4) {
-    const int rb = ti / ncb, cb = ti - rb * ncb;
-    const int r = rb * 16 + li, x = cb * 16 + li;
-    const int v = (even && r == h) ? -h : r;
-    int m = tw_index(v, lk, N);                  // (v, y = lk), advanced by 4 in y per step
-    const int st4 = ((8 * v) % (2 * N) + 2 * N) % (2 * N);
-    f32x4 qr = {0.f, 0.f, 0.f, 0.f}, qi = {0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < ldK; k0 += 4) {
-      const int y = k0 + lk;
-      float a_r = 0.f, a_i = 0.f, b = 0.f;
-      if (r < nrow && y < N) {
-        const float2 w = tw[m];                  // exp(-i k_v y')
-        a_r = w.x;
-        a_i = w.y;
-      }
-      if (y < N && x < N) b = d[y * N + x];
-      m += st4;
-      if (m >= 2 * N) m -= 2 * N;
-      qr = mfma16x16x4(a_r, b, qr);
-      qi = mfma16x16x4(a_i, b, qi);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = rb * 16 + 4 * lk + j;
-      if (row < nrow && x < ldK) Q[row * ldK + x] = make_float2(qr[j], qi[j]);
-    }
-  }
-  __syncthreads();
-  // pass B: tiles of D (16 rows v x 16 columns u = c - h), K = x
-  for (int ti = wave; ti < nrb * ncb; ti += 4) {
-    const int rb = ti / ncb, cb = ti - rb * ncb;
-    const int r = rb * 16 + li, c = cb * 16 + li;
-    int m = tw_index(c - h, lk, N);              // (u, x = lk), advanced by 4 in x per step
-    const int st4 = ((8 * (c - h)) % (2 * N) + 2 * N) % (2 * N);
-    f32x4 dr = {0.f, 0.f, 0.f, 0.f}, di = {0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < ldK; k0 += 4) {
-      const int x = k0 + lk;
-      const float2 q = (r < nrow) ? Q[r * ldK + x] : make_float2(0.f, 0.f);
-      float wr = 0.f, wi = 0.f;
-      if (x < N && c < N) {
-        const float2 w = tw[m];                  // exp(-i k_u x')
-        wr = w.x;
-        wi = w.y;
-      }
-      m += st4;
-      if (m >= 2 * N) m -= 2 * N;
-      dr = mfma16x16x4(q.x, wr, dr);
-      dr = mfma16x16x4(-q.y, wi, dr);
-      di = mfma16x16x4(q.x, wi, di);
-      di = mfma16x16x4(q.y, wr, di);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = rb * 16 + 4 * lk + j;
-      if (row < nrow && c < N) D[row * N + c] = make_float2(dr[j], di[j]);
-    }
-  }
-  __syncthreads();
-  // pair-slot order (slot_value_uv's scales, padding zero), then the
-  // Nyquist bins, then zero up to the even length
-  const SlotPlan sp = make_slot_plan_p(N, P);
-  float2* dst = out + bin_off[gal];
-  for (int b = threadIdx.x; b < sp.nbins; b += blockDim.x) {
-    int u, v;
-    float scale = 1.0f;
-    if (b < 2 * sp.nslots) {
-      if (!slot_value_uv(N, sp, b, u, v, scale)) {
-        dst[b] = make_float2(0.f, 0.f);
-        continue;
-      }
-    } else if (b < 2 * sp.nslots + sp.nspec) {
-      int cm;
-      nyq_bin_uv(N, b - 2 * sp.nslots, u, v, cm);
-    } else {
-      dst[b] = make_float2(0.f, 0.f);
-      continue;
-    }
-    const float2 z = D[((v < 0) ? h : v) * N + (u + h)];
-    dst[b] = make_float2(scale * z.x, scale * z.y);
-  }
-}
+constexpr size_t kMaxDftLds = 160 * 1024 - 64;     // beside the static scratch
 
 }  // namespace
 
 size_t render_mfma_lds_bytes(int N) { return render_mfma_lds(N); }
-size_t dft_bins_mfma_lds_bytes(int N) { return dft_mfma_lds(N); }
+hipError_t init_dft_tables(int device) {
+  static std::mutex m;
+  static bool done[kMaxDevices] = {};
+  if (device < 0 || device >= kMaxDevices) return hipErrorInvalidDevice;
+  std::lock_guard<std::mutex> lock(m);
+  if (done[device]) return hipSuccess;
+  hipStream_t s = nullptr;
+  hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(dft_tables_kernel, dim3(kMaxN - 7), dim3(256), 0, s);
+  e = hipGetLastError();
+  const hipError_t e2 = hipStreamSynchronize(s);
+  (void)hipStreamDestroy(s);
+  if (e == hipSuccess) e = e2;
+  done[device] = e == hipSuccess;
+  return e;
+}
+
+DftTab dft_tables(int N) {
+  static std::mutex m;
+  static void* ptr[kMaxDevices][2] = {};
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= kMaxDevices) return {nullptr, nullptr};
+  std::lock_guard<std::mutex> lock(m);
+  void** p = ptr[device];
+  if (!p[1]) {
+    if (hipGetSymbolAddress(&p[0], HIP_SYMBOL(dft_tab)) != hipSuccess) return {nullptr, nullptr};
+    if (hipGetSymbolAddress(&p[1], HIP_SYMBOL(sinc_tab)) != hipSuccess) return {nullptr, nullptr};
+  }
+  static const auto offs = [] {
+    std::array<int, kMaxN + 1> o{};
+    for (int n = 8; n < kMaxN; ++n) o[n + 1] = o[n] + dft_tab_len(n);
+    return o;
+  }();
+  return {static_cast<const float2*>(p[0]) + offs[N], static_cast<const double2*>(p[1]) + N * kSincLen};
+}
+
+size_t dft_bins_mfma_lds_bytes(int N, int P) {
+  const DftLds l = dft_lds(N, make_slot_plan_p(N, P));
+  return l.r + l.rows + (dft_big(N) ? 0 : l.tab);
+}
 
 hipError_t launch_dft_bins_mfma(const float* data, const double* model, const int32_t* gidx, int n,
                                 const int64_t* off, const int64_t* bin_off, int N, int P, float2* out,
                                 double* chi2, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  const size_t lds = dft_mfma_lds(N);
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
-  (void)hipFuncSetAttribute((const void*)dft_bins_mfma_kernel,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL(dft_bins_mfma_kernel, dim3(n), dim3(256), lds, s, data, model, gidx, off, bin_off, N,
-                     P, out, chi2);
+  const size_t lds = dft_bins_mfma_lds_bytes(N, P);
+  const DftTab t = dft_tables(N);
+  if (lds > kMaxDftLds || !t.dft) return hipErrorInvalidValue;
+  const int per = dft_per_wave(N);
+  auto kern = per == 1 ? dft_bins_mfma_kernel<1> : per == 2 ? dft_bins_mfma_kernel<2> : dft_bins_mfma_kernel<4>;
+  const int nw = dft_waves(N);
+  (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL(kern, dim3(dft_grid(n, nw, lds, per == 1 ? 5 : per == 2 ? 4 : 2)), dim3(kWave * nw), lds, s, data, model, gidx, n, off, bin_off,
+                     N, P, t.dft, out, chi2);
   return hipGetLastError();
 }
 

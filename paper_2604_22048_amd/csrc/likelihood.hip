@@ -1,151 +1,216 @@
-// Batched log-likelihood and gradient (eq. likelihood-pixels), one wave per
-// galaxy.  The DFT of the data (or, for the pixel method, of the pixel
-// residual) at the half-plane bins is staged in LDS and contracted with the
-// analytic spectrum by kspace_sums (the same routine the sampler uses).
+// Batched log-likelihood and gradient (eq. likelihood-pixels), one workgroup per
+// galaxy: the DFT of the stamp (or, for the pixel method, of the pixel
+// residual) at the half-plane bins is formed in LDS by all its waves
+// (dft_device.h) and contracted there with the analytic spectrum by one of
+// them (kspace_sums, the routine the sampler uses), so the spectrum never
+// leaves the workgroup.  With the direct transform, which is a kernel of its
+// own, the spectra are read from memory instead.
 #include <type_traits>
 
 #include "bsi_kernels.h"
-#include "kspace.h"
+#include "dft_device.h"
 
 namespace bsi {
 
-// MX: the sum over the galaxy's n_exp exposures (stamps gal n_exp + j, each
-// staged in turn) with per-bin noise weights sqw_all beside the spectrum
-// (Appendix C).
-template <int PROF, bool RESID, int P, bool MX = false>
-__global__ void __launch_bounds__(64) loglik_kernel(
-    const float2* __restrict__ dh_all, const int64_t* __restrict__ bin_off, const int32_t* __restrict__ gidx,
-    const float* __restrict__ params, const float* __restrict__ psf, const float* __restrict__ sigma,
-    int N, float rscale, float pscale_inv, float nu, const double* __restrict__ chi2_pix,
-    double* __restrict__ loglik, float* __restrict__ grad, uint32_t* __restrict__ status, int n_exp,
-    const float* __restrict__ sqw_all) {
-  static_assert(!(MX && RESID), "exposures: k-space form only");
-  extern __shared__ float4 smem4[];
+namespace {
+
+constexpr size_t kMaxLds = 160 * 1024 - 128;    // beside the static scratch
+
+// LDS: [stamp, then spectrum | sqrt-weights | column table | PSF-sinc table | row
+// bases | Ym, X, Yf | reduction scratch | DFT table]; only the column and
+// PSF-sinc tables, Ym, X, Yf and the scratch where the spectra come from memory.
+struct LoglikLds {
+  size_t sqw, cols, atab, rows, sep, red, tab, total;      // byte offsets
+};
+
+__host__ __device__ inline LoglikLds loglik_lds(int N, int P, bool mx, bool fused) {
   const Geom g = make_geom(N);
   const SlotPlan sp = make_slot_plan_p(N, P);
-  const int gal = gidx[blockIdx.x];
-  const int nbp = (sp.nbins + 1) & ~1;
-  float2* dh = reinterpret_cast<float2*>(smem4);
-  float* sqw = reinterpret_cast<float*>(dh + nbp);
-  float* atab = sqw + (MX ? (nbp + 3) & ~3 : 0);
-  float4* cols = reinterpret_cast<float4*>(atab + ((g.ntab + 3) & ~3));
-  float4* Ym = cols + sp.P * 64;
+  const DftLds f = dft_lds(N, sp);
+  auto up = [](size_t b) { return (b + 15) & ~(size_t)15; };
+  LoglikLds l;
+  l.sqw = fused ? f.r : 0;
+  l.cols = l.sqw + (fused && mx ? up(sizeof(float) * sp.nbins) : 0);
+  l.atab = l.cols + sizeof(float4) * sp.P * 64;
+  l.rows = l.atab + up(sizeof(float) * g.ntab);
+  l.sep = l.rows + (fused ? f.rows : 0);
+  l.red = l.sep + sizeof(float4) * sp.ymax + up(sizeof(float2) * (2 * g.ntab + 3));
+  l.tab = l.red + sizeof(float) * 64 * 8;
+  l.total = l.tab + (fused ? f.tab : 0);
+  return l;
+}
+
+// MX: the sum over the galaxy's n_exp exposures (stamps gal n_exp + j, each
+// transformed in turn) with per-bin noise weights (Appendix C).
+// U units of the transform per wave (dft_per_wave), or U = 0: the spectra come
+// from memory, one wave per galaxy.
+// Bound by the matrix cores (the transform's products, half of the time) and by
+// what runs beside them: 4 workgroups of 4 waves per compute unit at 53 px,
+// some contracting with one wave while the others transform.  10,000 galaxies
+// of 53 px: the call 183 us; transform and contraction as two kernels, with
+// the transform's factors looked up per element and the spectra (123 MB)
+// through memory and LDS, took 218 and 69.
+template <int PROF, bool RESID, int P, bool MX, int U>
+__global__ void __launch_bounds__(U == 0 ? kWave : 512, U == 0 ? 1 : P <= 4 ? 4 : 2) loglik_kernel(LoglikArgs a) {
+  static_assert(!(MX && RESID), "exposures: k-space form only");
+  extern __shared__ float4 smem4[];
+  __shared__ double red[8];
+  const int N = a.N;
+  const Geom g = make_geom(N);
+  const SlotPlan sp = make_slot_plan_p(N, P);
+  constexpr bool FUSED = U > 0;
+  const LoglikLds l = loglik_lds(N, P, MX, FUSED);
+  char* base = reinterpret_cast<char*>(smem4);
+  float* R = reinterpret_cast<float*>(base);
+  float* sqw_s = reinterpret_cast<float*>(base + l.sqw);
+  float4* cols = reinterpret_cast<float4*>(base + l.cols);
+  float* atab = reinterpret_cast<float*>(base + l.atab);
+  int* rows = reinterpret_cast<int*>(base + l.rows);
+  float2* tab = reinterpret_cast<float2*>(base + l.tab);
+  float4* Ym = reinterpret_cast<float4*>(base + l.sep);
   float2* X = reinterpret_cast<float2*>(Ym + sp.ymax);
   float2* Yf = X + g.ntab + 2;
-  float* red = reinterpret_cast<float*>(Yf + g.ntab + 1);
-  red = reinterpret_cast<float*>((reinterpret_cast<uintptr_t>(red) + 15) & ~uintptr_t(15));
+  float* scratch = reinterpret_cast<float*>(base + l.red);
+  if (FUSED) {
+    load_table(N, a.tab.dft, tab);
+    dft_row_bases(N, sp, rows);
+  }
   build_col_table(g, sp, cols);
-  const float* p = params + 6 * (int64_t)gal;
-  const float F = p[0], s = p[1], e1 = p[2], e2 = p[3], dx = p[4], dy = p[5];
-  const float E = e1 * e1 + e2 * e2;
-  uint32_t st = 0;
-  if (!(E < 1.0f) || !(s > 0.0f) || !(F > 0.0f)) st |= 1u;
-  const Shape sh = make_shape<PROF>(s * rscale, e1, e2, nu);
-  const LaneCols<P> lc = lane_cols<P>(cols);
-  const int ne = MX ? n_exp : 1;
-  KResult r{0.0, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  float sig = 1.0f;
-  for (int x = 0; x < ne; ++x) {
-    const int64_t stp = MX ? (int64_t)gal * ne + x : gal;    // this exposure's stamp
-    __syncthreads();
-    const float2* src = dh_all + bin_off[stp];
-    for (int b = threadIdx.x; b < sp.nbins; b += blockDim.x) dh[b] = src[b];
-    if constexpr (MX)
-      for (int b = threadIdx.x; b < sp.nbins; b += blockDim.x) sqw[b] = sqw_all[bin_off[stp] + b];
-    const float spsf = psf[stp] * 0.42466090014400953f * pscale_inv;
-    for (int t = threadIdx.x; t < g.ntab; t += blockDim.x) {
-      const int u = t - g.h;
-      const double k = 2.0 * 3.14159265358979323846 * u / N;
-      const double sn = (u == 0) ? 1.0 : sinpi((double)u / N) / (3.14159265358979323846 * u / N);
-      atab[t] = (float)(exp(-0.5 * (double)spsf * spsf * k * k) * sn);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), nw = blockDim.x / kWave;
+  const int ne = MX ? a.n_exp : 1;
+  for (int gi = blockIdx.x; gi < a.n; gi += gridDim.x) {
+    const int gal = a.gidx ? a.gidx[gi] : gi;
+    const float* p = a.params + 6 * (int64_t)gal;
+    const float F = p[0], s = p[1], e1 = p[2], e2 = p[3], dx = p[4], dy = p[5];
+    const float E = e1 * e1 + e2 * e2;
+    const Shape sh = make_shape<PROF>(s * a.rscale, e1, e2, a.nu);
+    KResult r{0.0, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float sig = 1.0f;
+    for (int x = 0; x < ne; ++x) {
+      const int64_t st = MX ? (int64_t)gal * ne + x : gal;    // this exposure's stamp
+      const int64_t o = a.off ? a.off[st] : st * N * N;
+      __syncthreads();                                        // the last stamp has been summed
+      double sq = 0.0;
+      if (FUSED) sq = load_stamp(N, a.data + o, RESID ? a.model + o : nullptr, R);
+      const float spsf = a.psf[st] * 0.42466090014400953f * a.pscale_inv;
+      for (int t = threadIdx.x; t < g.ntab; t += blockDim.x) {
+        const double2 ks = a.tab.sinc[t < g.h ? g.h - t : t - g.h];
+        atab[t] = (float)(exp(-0.5 * (double)spsf * spsf * ks.x * ks.x) * ks.y);
+      }
+      const float2* dh;
+      const float* sqw = nullptr;
+      if constexpr (FUSED) {
+        if (RESID) {
+          sq = wave_sum(sq);
+          if (lane_id() == 0) red[wave] = sq;
+        }
+        __syncthreads();
+        if (wave == nw - 1) fill_tables(g, sp, atab, X, Ym, Yf, F, dx, dy);
+        stamp_dft<U, MX>(N, sp, tab, R, rows, MX && a.noise_ps ? a.noise_ps + o : nullptr, sqw_s);
+        dh = reinterpret_cast<const float2*>(R);
+        if (MX) sqw = sqw_s;
+        __syncthreads();
+      } else {
+        // each lane reads its own slots, straight from memory
+        dh = a.dh + a.bin_off[st];
+        if (MX) sqw = a.sqw + a.bin_off[st];
+        __syncthreads();
+        fill_tables(g, sp, atab, X, Ym, Yf, F, dx, dy);
+      }
+      if (wave != 0) continue;
+      const LaneCols<P> lc = lane_cols<P>(cols);
+      sig = a.sigma[st];
+      const float norm = 1.0f / ((float)N * (float)N * sig * sig);
+      const KSums S = kspace_sums<PROF, P, RESID, true, 0, 1, 1, MX>(g, sp, lc, dh, X, Ym, Yf, sh, scratch, 0,
+                                                                     nullptr, sqw);
+      const KResult q = kspace_finish<PROF>(S, sh, F, s, e1, e2, norm);
+      r.loglik += q.loglik;
+      r.dF += q.dF;
+      r.ds += q.ds;
+      r.de1 += q.de1;
+      r.de2 += q.de2;
+      r.ddx += q.ddx;
+      r.ddy += q.ddy;
     }
-    __syncthreads();
-    sig = sigma[stp];
-    const float norm = 1.0f / ((float)N * (float)N * sig * sig);
-    fill_tables(g, sp, atab, X, Ym, Yf, F, dx, dy);
-    const KSums S = kspace_sums<PROF, P, RESID, true, 0, 1, 1, MX>(g, sp, lc, dh, X, Ym, Yf, sh, red, 0,
-                                                                   nullptr, sqw);
-    const KResult q = kspace_finish<PROF>(S, sh, F, s, e1, e2, norm);
-    r.loglik += q.loglik;
-    r.dF += q.dF;
-    r.ds += q.ds;
-    r.de1 += q.de1;
-    r.de2 += q.de2;
-    r.ddx += q.ddx;
-    r.ddy += q.ddy;
-  }
-  if (RESID) r.loglik = -0.5 * chi2_pix[gal] / ((double)sig * (double)sig);
-  if (!isfinite(r.loglik)) st |= 2u;
-  if (threadIdx.x == 0) {
-    if (loglik) loglik[gal] = r.loglik;
-    if (status) status[gal] = st;
-  }
-  if (grad && threadIdx.x < 6) {
-    const float v[6] = {r.dF, r.ds, r.de1, r.de2, r.ddx, r.ddy};
-    float o = v[0];
+    if (wave != 0) continue;
+    uint32_t st = 0;
+    if (!(E < 1.0f) || !(s > 0.0f) || !(F > 0.0f)) st |= 1u;
+    if (RESID) {
+      double chi2 = FUSED ? 0.0 : a.chi2[gal];
+      if (FUSED)
+        for (int w = 0; w < nw; ++w) chi2 += red[w];
+      r.loglik = -0.5 * chi2 / ((double)sig * (double)sig);
+    }
+    if (!isfinite(r.loglik)) st |= 2u;
+    if (threadIdx.x == 0) {
+      if (a.loglik) a.loglik[gal] = r.loglik;
+      if (a.status) a.status[gal] = st;
+    }
+    if (a.grad && threadIdx.x < 6) {
+      const float v[6] = {r.dF, r.ds, r.de1, r.de2, r.ddx, r.ddy};
+      float o = v[0];
 #pragma unroll
-    for (int j = 1; j < 6; ++j) o = (threadIdx.x == j) ? v[j] : o;
-    grad[6 * (int64_t)gal + threadIdx.x] = o;
+      for (int j = 1; j < 6; ++j) o = (threadIdx.x == j) ? v[j] : o;
+      a.grad[6 * (int64_t)gal + threadIdx.x] = o;
+    }
   }
 }
 
-static size_t loglik_lds_bytes(int N, int P, bool mx) {
-  const Geom g = make_geom(N);
-  const SlotPlan sp = make_slot_plan_p(N, P);
-  const int nbp = (sp.nbins + 1) & ~1;
-  return sizeof(float2) * nbp + sizeof(float) * (mx ? (nbp + 3) & ~3 : 0) +
-         sizeof(float) * ((g.ntab + 3) & ~3) +
-         sizeof(float4) * sp.P * 64 + sizeof(float4) * sp.ymax + sizeof(float2) * (2 * g.ntab + 3) +
-         16 + sizeof(float) * 64 * 8;
+template <int PROF, bool RESID, bool MX, int U>
+void launch_loglik_u(const LoglikArgs& a, hipStream_t s) {
+  const size_t lds = loglik_lds(a.N, a.P, MX, U > 0).total;
+  const int nw = U > 0 ? dft_waves(a.N) : 1;
+  const dim3 grid(U > 0 ? dft_grid(a.n, nw, lds, a.P <= 4 ? 4 : 2) : a.n), block(kWave * nw);
+  auto go = [&](auto kern) {
+    if (lds > 64 * 1024)
+      (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(kern, grid, block, lds, s, a);
+  };
+  switch (a.P) {
+    case 1: go(loglik_kernel<PROF, RESID, 1, MX, U>); break;
+    case 2: go(loglik_kernel<PROF, RESID, 2, MX, U>); break;
+    case 3: go(loglik_kernel<PROF, RESID, 3, MX, U>); break;
+    case 4: go(loglik_kernel<PROF, RESID, 4, MX, U>); break;
+    case 5: go(loglik_kernel<PROF, RESID, 5, MX, U>); break;
+    case 6: go(loglik_kernel<PROF, RESID, 6, MX, U>); break;
+    default: go(loglik_kernel<PROF, RESID, 8, MX, U>); break;
+  }
 }
 
 template <int PROF, bool RESID, bool MX>
-static void launch_loglik_p(int P, dim3 grid, size_t lds, hipStream_t s, const float2* dh,
-                            const int64_t* bin_off, const int32_t* gidx, const float* params,
-                            const float* psf, const float* sigma, int N, float rscale,
-                            float pscale_inv, float nu, const double* chi2_pix, double* loglik,
-                            float* grad, uint32_t* status, int n_exp, const float* sqw) {
-  auto go = [&](auto kern) {
-    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(kern, grid, dim3(64), lds, s, dh, bin_off, gidx, params, psf, sigma, N,
-                       rscale, pscale_inv, nu, chi2_pix, loglik, grad, status, n_exp, sqw);
-  };
-  switch (P) {
-    case 1: go(loglik_kernel<PROF, RESID, 1, MX>); break;
-    case 2: go(loglik_kernel<PROF, RESID, 2, MX>); break;
-    case 3: go(loglik_kernel<PROF, RESID, 3, MX>); break;
-    case 4: go(loglik_kernel<PROF, RESID, 4, MX>); break;
-    case 5: go(loglik_kernel<PROF, RESID, 5, MX>); break;
-    case 6: go(loglik_kernel<PROF, RESID, 6, MX>); break;
-    default: go(loglik_kernel<PROF, RESID, 8, MX>); break;
-  }
+void launch_loglik_p(const LoglikArgs& a, hipStream_t s) {
+  if (!a.data) launch_loglik_u<PROF, RESID, MX, 0>(a, s);
+  else if (dft_per_wave(a.N) == 1) launch_loglik_u<PROF, RESID, MX, 1>(a, s);
+  else launch_loglik_u<PROF, RESID, MX, 2>(a, s);
 }
 
-hipError_t launch_loglik(const float2* dh, const int64_t* bin_off, const int32_t* gidx, int n,
-                         const float* params, const float* psf, const float* sigma, int N, int P,
-                         float rscale, float pscale_inv, int prof, float nu, int resid_mode,
-                         const double* chi2_pix, double* loglik, float* grad, uint32_t* status,
-                         hipStream_t s, int n_exp, const float* sqw) {
-  if (n <= 0) return hipSuccess;
-  if (!plan_valid(N, P)) return hipErrorInvalidValue;
-  const bool mx = sqw != nullptr;
-  if (mx && (resid_mode || n_exp < 1)) return hipErrorInvalidValue;
-  const size_t lds = loglik_lds_bytes(N, P, mx);
-  const dim3 grid(n);
+}  // namespace
+
+// One kernel wherever its waves hold one unit of the transform (up to 64 px):
+// 53 px, 1 stamp 19 us against 32 in two kernels, 1,000 27 / 44, 10,000 183 /
+// 184 (calls, host included).  Larger stamps leave one or two of its
+// workgroups per compute unit, which idle while one wave contracts: 73 px,
+// 1,000 stamps 65 / 75 us, 2,000 117 / 116, 4,000 220 / 204; 101 px, 500 73 / 88,
+// 1,000 136 / 139, 2,000 253 / 232.
+bool loglik_fused(int N, int P, bool mx, int stamps) {
+  return !dft_big(N) && loglik_lds(N, P, mx, true).total <= kMaxLds && (dft_per_wave(N) == 1 || stamps <= 1024);
+}
+
+hipError_t launch_loglik(LoglikArgs a, int prof, bool resid, bool mx, hipStream_t s) {
+  if (a.n <= 0) return hipSuccess;
+  if (!plan_valid(a.N, a.P)) return hipErrorInvalidValue;
+  if (mx && (resid || a.n_exp < 1)) return hipErrorInvalidValue;
+  if (loglik_lds(a.N, a.P, mx, a.data != nullptr).total > kMaxLds) return hipErrorInvalidValue;
+  a.tab = dft_tables(a.N);
+  if (!a.tab.dft) return hipErrorInvalidValue;
   auto run = [&](auto prof_tag) {
     constexpr int PR = decltype(prof_tag)::value;
     if (mx)
-      launch_loglik_p<PR, false, true>(P, grid, lds, s, dh, bin_off, gidx, params, psf, sigma, N,
-                                       rscale, pscale_inv, nu, chi2_pix, loglik, grad, status, n_exp,
-                                       sqw);
-    else if (resid_mode)
-      launch_loglik_p<PR, true, false>(P, grid, lds, s, dh, bin_off, gidx, params, psf, sigma, N,
-                                       rscale, pscale_inv, nu, chi2_pix, loglik, grad, status, 1,
-                                       nullptr);
+      launch_loglik_p<PR, false, true>(a, s);
+    else if (resid)
+      launch_loglik_p<PR, true, false>(a, s);
     else
-      launch_loglik_p<PR, false, false>(P, grid, lds, s, dh, bin_off, gidx, params, psf, sigma, N,
-                                        rscale, pscale_inv, nu, chi2_pix, loglik, grad, status, 1,
-                                        nullptr);
+      launch_loglik_p<PR, false, false>(a, s);
   };
   if (prof == kProfExp)
     run(std::integral_constant<int, kProfExp>());
