@@ -125,7 +125,11 @@ def render_stamps(batch: Batch, params: torch.Tensor, lib: Library | None = None
     lib = lib or get(params.device.index or 0)
     params = params.contiguous().float()
     assert params.shape == (batch.n_gal, 6)
-    out = torch.zeros(batch.n_pixels, dtype=torch.float32, device=params.device)
+    # every pixel is written where the stamps lie back to back; gaps are zero
+    end = batch.off + batch.n.astype(np.int64) ** 2
+    packed = batch.n_gal > 0 and batch.off[0] == 0 and np.array_equal(batch.off[1:], end[:-1])
+    alloc = torch.empty if packed else torch.zeros
+    out = alloc(batch.n_pixels, dtype=torch.float32, device=params.device)
     b = batch.c()
     lib.check(lib.lib.bsi_render_stamps(lib.h, C.byref(b), _ptr(params), _ptr(out),
                                         _stream(params.device)), "bsi_render_stamps")

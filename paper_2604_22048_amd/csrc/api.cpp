@@ -361,25 +361,21 @@ int bsi_render_stamps(bsi_handle h, const bsi_batch* batch, const float* params,
   (void)hipSetDevice(h->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool cap = capturing(s);
-  const Plan p = make_plan(h, batch);
+  const Plan p = make_plan(h, batch, transform_of(h, batch->n[0]) == BSI_TRANSFORM_MFMA);
   const PlanBytes pb = plan_bytes(batch, p);
-  if ((rc = prepare(h, s, cap, {{&h->gidx, pb.gidx}, {&h->off, pb.off}, {&h->bin_off, pb.bin_off},
-                                {&h->ggidx, pb.ggidx}}, pb.stage())))
+  if (!p.packed && (rc = prepare(h, s, cap, {{&h->gidx, pb.gidx}, {&h->off, pb.off}, {&h->bin_off, pb.bin_off},
+                                             {&h->ggidx, pb.ggidx}}, pb.stage())))
     return rc;
   if ((rc = upload_plan(h, batch, p, s, cap))) return rc;
   const float rs = profile_rscale(batch->profile, batch->pixel_scale, batch->spergel_nu);
-  for (const ClassRange& c : p.classes) {
-    const int32_t* gi = gidx_ptr(h, p, c);
-    const int64_t* off = static_cast<const int64_t*>(h->off.p);
-    hipError_t e = transform_of(h, c.N) == BSI_TRANSFORM_MFMA
-        ? launch_render_mfma(params, batch->psf_fwhm, gi, c.count, off, c.N, rs,
-                             1.0f / batch->pixel_scale, batch->profile, batch->spergel_nu, out, s,
-                             p.E)
-        : launch_render(params, batch->psf_fwhm, gi, c.count, off, c.N, rs,
-                        1.0f / batch->pixel_scale, batch->profile, batch->spergel_nu, out, s, p.E);
-    if (e != hipSuccess) return hip_fail(h, e, "render launch");
-  }
-  return finish(h, s, cap);
+  const int64_t* off = p.packed ? nullptr : static_cast<const int64_t*>(h->off.p);
+  hipError_t e = for_classes(h, p, s, cap, [&](const ClassRange& c, hipStream_t st) {
+    auto launch = transform_of(h, c.N) == BSI_TRANSFORM_MFMA ? launch_render_mfma : launch_render;
+    return launch(params, batch->psf_fwhm, gidx_ptr(h, p, c), c.count, off, c.N, rs, 1.0f / batch->pixel_scale,
+                  batch->profile, batch->spergel_nu, out, st, p.E);
+  });
+  if (e != hipSuccess) return hip_fail(h, e, "render launch");
+  return p.packed ? BSI_OK : finish(h, s, cap);
 }
 
 int bsi_loglik_grad(bsi_handle h, const bsi_batch* batch, const float* data, const float* params,

@@ -27,7 +27,6 @@ inline float profile_rscale(int prof, float pixel_scale, float nu = 0.5f) {
 // ---- transform.hip ----
 size_t dft_bins_lds_bytes(int N);
 size_t render_lds_bytes(int N);
-size_t render_mfma_lds_bytes(int N);
 size_t dft_bins_mfma_lds_bytes(int N, int P);
 // DFT operand and PSF-sinc tables of one stamp side (dft_device.h), the current
 // device's: filled by init_dft_tables, once per device.
@@ -57,9 +56,10 @@ hipError_t launch_dft_bins(const float* data, const double* model, const int32_t
 hipError_t launch_render(const float* params, const float* psf, const int32_t* gidx, int n,
                          const int64_t* off, int N, float rscale, float pscale_inv, int prof, float nu,
                          float* out, hipStream_t s, int n_exp = 1);
+// The model stamps in float64 throughout (matrix cores; the pixel-space likelihood).
 hipError_t launch_render_f64(const float* params, const float* psf, const int32_t* gidx, int n,
                              const int64_t* off, int N, float rscale, float pscale_inv, int prof, float nu,
-                             double* out, hipStream_t s, int n_exp = 1);
+                             double* out, hipStream_t s);
 
 // Whitened spectrum and per-bin sqrt-weights for stationary correlated noise.
 hipError_t launch_whiten(const float* noise_ps, const int32_t* gidx, int n, const int64_t* off,

@@ -106,6 +106,8 @@ __device__ __forceinline__ void dft_row_bases(int N, const SlotPlan& sp, int* ro
 
 constexpr int kWaitVmcnt0 = 0x0F70;   // every vector memory operation done (gfx9 wait counter)
 
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(kWaitVmcnt0); }
+
 // Load stamp `data` (minus `model`, both at the stamp's first pixel) into d and
 // zero its rows up to a whole K step; the caller synchronises.  Returns this
 // thread's part of sum (data - model)^2.  Without a model the pixels (and
@@ -123,7 +125,7 @@ __device__ __forceinline__ double load_stamp(int N, const float* __restrict__ da
       sq = fma(x, x, sq);
     }
     for (int t = n + threadIdx.x; t < full; t += blockDim.x) d[t] = 0.f;
-    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    wait_loads();
     return sq;
   }
   // the last transfer is ragged: its idle lanes repeat the last pixel past the
@@ -131,7 +133,7 @@ __device__ __forceinline__ double load_stamp(int N, const float* __restrict__ da
   int t = w0;
   for (; t < n; t += blockDim.x)
     __builtin_amdgcn_global_load_lds(data + min(t + lane, n - 1), d + t, 4, 0, 0);
-  __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+  wait_loads();
   if (t - (int)blockDim.x <= n - 1 && t - (int)blockDim.x + kWave >= n && w0 < n)
     for (int z = n + lane; z < full; z += kWave) d[z] = 0.f;
   return sq;
@@ -146,12 +148,12 @@ __device__ __forceinline__ float touch_stamp(int N, const float* __restrict__ da
 
 __device__ __forceinline__ void touch_done(float x) { asm volatile("" ::"v"(x)); }
 
-// Copy side N's table into LDS (16 bytes per lane; with the stamp's wait).
-__device__ __forceinline__ void load_table(int N, const float2* __restrict__ tab, float2* t) {
-  const DftDims g = dft_dims(N);
+// Copy a table of `entries` (a multiple of 64) into LDS, 16 bytes per lane (with
+// the stamp's wait).
+__device__ __forceinline__ void load_table(const float2* __restrict__ tab, float2* t, int entries) {
   const int lane = lane_id(), w0 = __builtin_amdgcn_readfirstlane(threadIdx.x - lane);
-  // a step's 512 bytes are half a wave's transfer; an odd count ends in the padding
-  for (int i = 2 * w0; i < g.nblk * g.steps * 64; i += 2 * blockDim.x)
+  // 64 entries are half a wave's transfer; an odd count ends in the padding
+  for (int i = 2 * w0; i < entries; i += 2 * blockDim.x)
     __builtin_amdgcn_global_load_lds(tab + i + 2 * lane, t + i, 16, 0, 0);
 }
 

@@ -72,7 +72,7 @@ __global__ void __launch_bounds__(U == 0 ? kWave : 512, U == 0 ? 1 : P <= 4 ? 4 
   float2* Yf = X + g.ntab + 2;
   float* scratch = reinterpret_cast<float*>(base + l.red);
   if (FUSED) {
-    load_table(N, a.tab.dft, tab);
+    load_table(a.tab.dft, tab, dft_tab_len(N));
     dft_row_bases(N, sp, rows);
   }
   build_col_table(g, sp, cols);

@@ -156,12 +156,10 @@ __device__ __forceinline__ void build_twiddles_f64(double2* tw, int N) {
 // The whole render runs in float64 (it is off the sampling path): the
 // spectrum row of one v is built in LDS, transformed along x into the
 // half-transform B[v][x], and B is then summed along y.
-// OutT = double keeps the stamp unrounded for the pixel-space likelihood.
-template <typename OutT>
 __global__ void __launch_bounds__(256) render_kernel(
     const float* __restrict__ params, const float* __restrict__ psf_fwhm, const int32_t* __restrict__ gidx,
     const int64_t* __restrict__ off, int N, float rscale, float pscale_inv, int prof, float nu,
-    int n_exp, OutT* __restrict__ out) {
+    int n_exp, float* __restrict__ out) {
   extern __shared__ double2 smemd[];
   const int gal = gidx[blockIdx.x];
   const int h = N / 2, ntab = 2 * h + 1, nrow = h + 1;
@@ -209,7 +207,7 @@ __global__ void __launch_bounds__(256) render_kernel(
       const double2 w = tw[tw_index(r, j, N)];
       acc += b.x * w.x + b.y * w.y;                    // Re(b * conj(w))
     }
-    out[o + t] = (OutT)(acc * inv);
+    out[o + t] = (float)(acc * inv);
   }
 }
 
@@ -231,29 +229,15 @@ hipError_t launch_dft_bins(const float* data, const double* model, const int32_t
   return hipGetLastError();
 }
 
-template <typename OutT>
-static hipError_t render_impl(const float* params, const float* psf, const int32_t* gidx, int n,
-                              const int64_t* off, int N, float rscale, float pscale_inv, int prof, float nu,
-                              int n_exp, OutT* out, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  const size_t lds = render_lds_bytes(N);
-  (void)hipFuncSetAttribute((const void*)render_kernel<OutT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                      (int)lds);
-  hipLaunchKernelGGL(render_kernel<OutT>, dim3(n), dim3(256), lds, s, params, psf, gidx, off, N,
-                     rscale, pscale_inv, prof, nu, n_exp, out);
-  return hipGetLastError();
-}
-
 hipError_t launch_render(const float* params, const float* psf, const int32_t* gidx, int n,
                          const int64_t* off, int N, float rscale, float pscale_inv, int prof, float nu,
                          float* out, hipStream_t s, int n_exp) {
-  return render_impl(params, psf, gidx, n, off, N, rscale, pscale_inv, prof, nu, n_exp, out, s);
-}
-
-hipError_t launch_render_f64(const float* params, const float* psf, const int32_t* gidx, int n,
-                             const int64_t* off, int N, float rscale, float pscale_inv, int prof, float nu,
-                             double* out, hipStream_t s, int n_exp) {
-  return render_impl(params, psf, gidx, n, off, N, rscale, pscale_inv, prof, nu, n_exp, out, s);
+  if (n <= 0) return hipSuccess;
+  const size_t lds = render_lds_bytes(N);
+  (void)hipFuncSetAttribute((const void*)render_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL(render_kernel, dim3(n), dim3(256), lds, s, params, psf, gidx, off, N,
+                     rscale, pscale_inv, prof, nu, n_exp, out);
+  return hipGetLastError();
 }
 
 // Noise weights of stationary correlated noise (Appendix C): every bin of
