@@ -21,10 +21,13 @@ class LogLik(torch.autograd.Function):
         ll, grad, status = api.loglik_grad(batch, data, params.detach(), method)
         ctx.save_for_backward(grad)
         ctx.mark_non_differentiable(status)
+        ctx.set_materialize_grads(False)      # no zeros for status
         return ll, status
 
     @staticmethod
     def backward(ctx, g_ll, g_status):
+        if g_ll is None:
+            return None, None, None, None
         (grad,) = ctx.saved_tensors
         return (g_ll.to(grad.dtype)[:, None] * grad, None, None, None)
 

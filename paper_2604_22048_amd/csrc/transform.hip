@@ -293,7 +293,7 @@ double exponential_hlr_factor() {
   return x;
 }
 
-double spergel_hlr_factor(double nu) {
+static double spergel_root(double nu) {
   // x^(nu+1) K_(nu+1)(x) falls from 2^nu Gamma(nu+1) at 0 to 0; bisect for half of that
   const double target = std::tgamma(nu + 1.0) * std::pow(2.0, nu - 1.0);
   auto f = [&](double x) { return std::pow(x, nu + 1.0) * std::cyl_bessel_k(nu + 1.0, x) - target; };
@@ -304,6 +304,16 @@ double spergel_hlr_factor(double nu) {
     (f(mid) > 0.0 ? lo : hi) = mid;
   }
   return 0.5 * (lo + hi);
+}
+
+double spergel_hlr_factor(double nu) {
+  // every call of a fit asks for the same index: the last one's root is kept
+  thread_local double last_nu = 0.5, last = spergel_root(0.5);
+  if (nu != last_nu) {
+    last = spergel_root(nu);
+    last_nu = nu;
+  }
+  return last;
 }
 
 }  // namespace bsi
