@@ -319,8 +319,7 @@ int bsi_create(bsi_handle* out, int32_t device, const char* tune_cache) {
       return BSI_EINVAL;
     }
   }
-  bool ok = hipStreamCreate(&h->own) == hipSuccess &&
-            hipEventCreateWithFlags(&h->ev_fork, hipEventDisableTiming) == hipSuccess &&
+  bool ok = hipEventCreateWithFlags(&h->ev_fork, hipEventDisableTiming) == hipSuccess &&
             hipEventCreateWithFlags(&h->ev_done, hipEventDisableTiming) == hipSuccess &&
             hipEventCreateWithFlags(&h->ev_stage, hipEventDisableTiming) == hipSuccess;
   // the auxiliary streams do not synchronise implicitly with the null stream:
@@ -330,6 +329,19 @@ int bsi_create(bsi_handle* out, int32_t device, const char* tune_cache) {
   for (int i = 0; ok && i < kAuxStreams; ++i)
     ok = hipStreamCreateWithFlags(&h->aux[i], hipStreamNonBlocking) == hipSuccess &&
          hipEventCreateWithFlags(&h->ev_join[i], hipEventDisableTiming) == hipSuccess;
+  // A process has four hardware queues; a new stream takes the one with the
+  // fewest streams, the youngest of several.  The null stream holds the first
+  // queue, the auxiliary streams now hold the other three, and the handle's own
+  // stream is to share the null stream's, so that a fork from either runs its
+  // four branches on four queues: as many short-lived streams come before it.
+  // (With `own` created first two auxiliary streams shared a queue, and a
+  // round of five stamp sides ended 0.9 ms later than its longest side.)
+  hipStream_t fill[kAuxStreams] = {};
+  for (int i = 0; ok && i < kAuxStreams; ++i)
+    ok = hipStreamCreateWithFlags(&fill[i], hipStreamNonBlocking) == hipSuccess;
+  ok = ok && hipStreamCreate(&h->own) == hipSuccess;
+  for (hipStream_t f : fill)
+    if (f) (void)hipStreamDestroy(f);
   if (!ok) {
     (void)hipGetLastError();
     bsi_destroy(h);
@@ -576,6 +588,7 @@ int bsi_hmc_sample(bsi_handle h, const bsi_batch* batch, const float* data, cons
   a.off = static_cast<const int64_t*>(h->off.p);
   a.nuts = nuts ? 1 : 0;
   a.max_depth = cfg->max_tree_depth;
+  a.n_side = batch->n_gal;
 
   const int T = a.t_stop;
   const bool plain = cfg->form == BSI_FORM_PLAIN;

@@ -163,21 +163,31 @@ __device__ __forceinline__ double wave_total(double x) {
 // then adds the partials of value l / 8 held by lanes 8 (l % 8) .. 8 (l % 8) + 7,
 // and a three-step DPP prefix sum inside each group of eight lanes finishes
 // the sum on lane 8 v + 7.  scratch must be 16-byte aligned, 2 KiB per wave.
+// (wave_gather7: the adds, of partials that are in the scratch already.)
+__device__ __forceinline__ void wave_gather7(float* v, const float* scratch) {
+  const int lane = lane_id();
+  const int val = lane >> 3, grp = lane & 7;
+  float t[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) t[k] = scratch[(8 * grp + k) * 8 + val];
+  __builtin_amdgcn_sched_barrier(0);   // the reads together, ahead of the adds
+  float acc = 0.f;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) acc += t[k];
+  acc = dpp_shift_add<0x111, 0xf>(acc);   // row_shr:1
+  acc = dpp_shift_add<0x112, 0xf>(acc);   // row_shr:2
+  acc = dpp_shift_add<0x114, 0xf>(acc);   // row_shr:4
+#pragma unroll
+  for (int j = 0; j < 7; ++j) v[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(acc), 8 * j + 7));
+}
+
 __device__ __forceinline__ void wave_total7(float* v, float* scratch) {
   const int lane = lane_id();
   float4* s4 = reinterpret_cast<float4*>(scratch);
   s4[2 * lane] = make_float4(v[0], v[1], v[2], v[3]);
   s4[2 * lane + 1] = make_float4(v[4], v[5], v[6], 0.f);
   wave_lds_sync();
-  const int val = lane >> 3, grp = lane & 7;
-  float acc = 0.f;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) acc += scratch[(8 * grp + k) * 8 + val];
-  acc = dpp_shift_add<0x111, 0xf>(acc);   // row_shr:1
-  acc = dpp_shift_add<0x112, 0xf>(acc);   // row_shr:2
-  acc = dpp_shift_add<0x114, 0xf>(acc);   // row_shr:4
-#pragma unroll
-  for (int j = 0; j < 7; ++j) v[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(acc), 8 * j + 7));
+  wave_gather7(v, scratch);
   wave_lds_sync();
 }
 
@@ -227,29 +237,41 @@ __device__ __forceinline__ double group_total(double x) {
 // LV = LS / 8 lanes per value, lane r of a chain adds value r / LV of lanes
 // 8 (r % LV) .. 8 (r % LV) + 7 of its chain, a DPP prefix sum inside each
 // group of LV lanes finishes the sum on its last lane, and the sums go back
-// through LDS to every lane of their chain.
+// through LDS to every lane of their chain.  (group_gather7: the adds, of
+// partials that are in the scratch already; the sums go back through out, at
+// least 32 floats, which may be the scratch itself.)
 template <int H>
-__device__ __forceinline__ void group_total7(float* v, float* scratch) {
+__device__ __forceinline__ void group_gather7(float* v, const float* scratch, float* out) {
   static_assert(H == 2 || H == 4, "several chains per wave");
   constexpr int LS = kWave / H, LV = LS / 8;
+  const int lane = lane_id();
+  const int base = lane & ~(LS - 1), r = lane & (LS - 1);
+  const int val = r / LV, grp = r % LV;
+  float t[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) t[k] = scratch[(base + 8 * grp + k) * 8 + val];
+  __builtin_amdgcn_sched_barrier(0);   // the reads together, ahead of the adds
+  float acc = 0.f;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) acc += t[k];
+  acc = dpp_shift_add<0x111, 0xf>(acc);                        // row_shr:1
+  if constexpr (LV == 4) acc = dpp_shift_add<0x112, 0xf>(acc);  // row_shr:2
+  wave_lds_sync();
+  if (grp == LV - 1) out[base / LV + val] = acc;
+  wave_lds_sync();
+  const float* res = out + base / LV;
+#pragma unroll
+  for (int j = 0; j < 7; ++j) v[j] = res[j];
+}
+
+template <int H>
+__device__ __forceinline__ void group_total7(float* v, float* scratch) {
   const int lane = lane_id();
   float4* s4 = reinterpret_cast<float4*>(scratch);
   s4[2 * lane] = make_float4(v[0], v[1], v[2], v[3]);
   s4[2 * lane + 1] = make_float4(v[4], v[5], v[6], 0.f);
   wave_lds_sync();
-  const int base = lane & ~(LS - 1), r = lane & (LS - 1);
-  const int val = r / LV, grp = r % LV;
-  float acc = 0.f;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) acc += scratch[(base + 8 * grp + k) * 8 + val];
-  acc = dpp_shift_add<0x111, 0xf>(acc);                        // row_shr:1
-  if constexpr (LV == 4) acc = dpp_shift_add<0x112, 0xf>(acc);  // row_shr:2
-  wave_lds_sync();
-  if (grp == LV - 1) scratch[base / LV + val] = acc;
-  wave_lds_sync();
-  const float* res = scratch + base / LV;
-#pragma unroll
-  for (int j = 0; j < 7; ++j) v[j] = res[j];
+  group_gather7<H>(v, scratch, scratch);
   wave_lds_sync();
 }
 

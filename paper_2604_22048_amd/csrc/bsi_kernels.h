@@ -130,6 +130,7 @@ struct HmcArgs {
   const int64_t* bin_off;
   const int32_t* gidx;
   int n_gal;              // galaxies in this launch (entries of gidx)
+  int n_side;             // galaxies of all launches that run side by side with it (0: this one alone)
   const float* psf;
   const float* sigma;
   const float* ref_xy;

@@ -35,9 +35,10 @@ struct DevBuf {
   size_t n = 0;
 };
 
-constexpr int kAuxStreams = 4;
-// streams of a forked launch: the caller's and up to kAuxStreams auxiliary
+// streams of a forked launch: the caller's and the auxiliary ones (a process
+// has four hardware queues)
 constexpr int kForkStreams = 4;
+constexpr int kAuxStreams = kForkStreams - 1;
 
 // An instantiated graph whose replays were enqueued; destroyed once `done`
 // (recorded after the last replay) has completed.

@@ -18,6 +18,7 @@
 //   adapted by dual averaging (Hoffman & Gelman 2014, Algorithm 5) on
 //   alpha = min(1, exp(-dH)).
 #include <algorithm>
+#include <type_traits>
 
 #include "bsi_kernels.h"
 #include "kspace.h"
@@ -42,6 +43,7 @@ struct GalCtx {
   const float4* cols;   // the workgroup's pair-slot column table
   int part;        // this wave's index among the W waves of its chain
   float* xch;      // the chain's partial-sum exchange area (2 x W x 12 floats)
+  TeamLds team;    // exchange areas of a team (team kernels)
   float norm;      // 1 / (N^2 sigma^2)
   float rscale;
   float nu;        // Spergel index (Spergel profile only)
@@ -110,8 +112,9 @@ __device__ __forceinline__ void add_result(KResult& r, const KResult& q) {
   r.ddy += q.ddy;
 }
 
-template <int PROF, int P, bool CHI2 = true, int NFIX = 0, int W = 1, int H = 1, bool MX = false>
-__device__ __forceinline__ double potential(const GalCtx& c, const LaneCols<P * H>& lc, const Prior& pr,
+template <int PROF, int P, bool CHI2 = true, int NFIX = 0, int W = 1, int H = 1, bool MX = false,
+          class Cols = LaneCols<P * H>>
+__device__ __forceinline__ double potential(const GalCtx& c, const Cols& lc, const Prior& pr,
                                             const float* th, float* gU, uint32_t& status,
                                             float* xbuf = nullptr) {
   const bool inside = in_support(th, pr);
@@ -143,6 +146,11 @@ __device__ __forceinline__ double potential(const GalCtx& c, const LaneCols<P * 
       const float sj = c.sig[j];
       add_result(r, kspace_finish<PROF>(S, sh, F, s, e1, e2, 1.0f / (n2 * sj * sj)));
     }
+  } else if constexpr (!std::is_same_v<Cols, LaneCols<P * H>>) {
+    fill_team(lc, c.g, c.X, c.Ym, F, dx, dy);
+    const KSums S =
+        kspace_sums_team<PROF, P, CHI2, NFIX, H>(lc, c.cols, c.dh, c.X, c.Ym, sh, c.team, c.part);
+    r = kspace_finish<PROF>(S, sh, F, s, e1, e2, c.norm);
   } else {
     fill_tables<H>(c.g, c.sp, c.atab, c.X, c.Ym, c.Yf, F, dx, dy);
     KSums S;
@@ -269,9 +277,9 @@ __device__ void fisher_inv_mass(const GalCtx& c, const Prior& pr, const float* t
 
 // LDS strides of one exposure (MX kernels): spectrum (float2), sqrt-weights
 // and PSF-sinc table (floats), each a multiple of 16 bytes.
-__host__ __device__ inline int dh_stride(const SlotPlan& sp) { return (sp.nbins + 1) & ~1; }
-__host__ __device__ inline int sw_stride(const SlotPlan& sp) { return (dh_stride(sp) + 3) & ~3; }
-__host__ __device__ inline int atab_stride(const Geom& g) { return (g.ntab + 3) & ~3; }
+__host__ __device__ constexpr int dh_stride(const SlotPlan& sp) { return (sp.nbins + 1) & ~1; }
+__host__ __device__ constexpr int sw_stride(const SlotPlan& sp) { return (dh_stride(sp) + 3) & ~3; }
+__host__ __device__ constexpr int atab_stride(const Geom& g) { return (g.ntab + 3) & ~3; }
 
 // Stage one galaxy's data spectrum and PSF-sinc table in LDS; MX: those of
 // each of its E exposures (stamps gal E + j), and the sqrt-weights.
@@ -327,7 +335,7 @@ __host__ __device__ inline int wave_table_len(const Geom& g, const SlotPlan& sp)
 
 // Four chains per wave (odd N only): Ym and X (padded to an even length),
 // no Nyquist table.
-__host__ __device__ inline int quad_table_len(const Geom& g, const SlotPlan& sp) {
+__host__ __device__ constexpr int quad_table_len(const Geom& g, const SlotPlan& sp) {
   return (2 * sp.ymax + g.ntab + 3) & ~1;
 }
 
@@ -504,11 +512,11 @@ __device__ __forceinline__ void lane0_sync() { wave_lds_sync(); }
 
 // H = 2 or 4: several chains per wave, each group of 64 / H lanes running its
 // own chain (its own record cs, tables and outputs); lane below is the lane
-// within the group.
-template <int PROF, int P, int NFIX, int W, int H = 1, bool MX = false>
-__device__ void advance_chain(const HmcArgs& a, const GalCtx& c, const LaneCols<P * H>& lc,
-                              const Prior& pr, ChainState* cs, float* samples_chain,
-                              float* trace_chain) {
+// within the group.  Cols: the lane's columns, TeamCols in a team (whose waves
+// run the same chains, each on its own copy of the records).
+template <int PROF, int P, int NFIX, int W, int H = 1, bool MX = false, class Cols = LaneCols<P * H>>
+__device__ void advance_chain(const HmcArgs& a, const GalCtx& c, const Cols& lc, const Prior& pr,
+                              ChainState* cs, float* samples_chain, float* trace_chain) {
   const int lane = chain_lane<H>();
   const uint32_t uid = cs->uid;
   int nev = 0;           // evaluations so far (alternates the exchange buffers)
@@ -1309,6 +1317,85 @@ __global__ void __launch_bounds__(MAXT, (MAXT > 256 ? 1 : kHmcWavesPerEu)) hmc_k
   }
 }
 
+// ---- Trajectories by teams ---------------------------------------------------
+
+// LDS: [team exchange areas | data spectrum | atab | column table | T H chain
+// records | H table sets without the Nyquist table].
+constexpr size_t team_lds_bytes(int N, int P, int H) {
+  const Geom g = make_geom(N);
+  const SlotPlan sp = make_slot_plan_p(N, P);
+  const int T = team_waves(P * H);
+  return sizeof(float) * team_floats(sp.nsr, P * H, H) + sizeof(float2) * dh_stride(sp) +
+         sizeof(float) * atab_stride(g) + sizeof(float4) * sp.P * 64 + sizeof(ChainState) * T * H +
+         sizeof(float2) * quad_table_len(g, sp) * H;
+}
+
+// One workgroup of T waves per group of H chains (the chains that share a wave
+// in hmc_kernel): fixed-length trajectories, one exposure, odd stamp sides.
+// For launches with fewer chain groups than the chip has SIMDs: an evaluation
+// of four chains at 53 px takes one wave 5.3 us, most of it the wave's own
+// instruction issue; a team's 2.6 us are the longest wave's issue (12 pairs of 42
+// instructions at 4 cycles, 0.85 us), the serial part that every wave repeats and
+// the three barriers.
+template <int PROF, int P, int NFIX, int H>
+__global__ void __launch_bounds__(kWave * team_waves(P * H), kHmcWavesPerEu) hmc_team_kernel(HmcArgs a) {
+  constexpr int T = team_waves(P * H);
+  constexpr Geom g = make_geom(NFIX);
+  constexpr SlotPlan sp = make_slot_plan_p(NFIX, P);
+  extern __shared__ float4 smem4[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int groups = a.C / H;
+  const int gal = a.gidx[blockIdx.x / groups];
+  const int ch = lane_id() / (kWave / H);                    // chain within the group
+  const int cw = (int)(blockIdx.x % groups) * H + ch;        // chain of the galaxy
+  float2* dh = reinterpret_cast<float2*>(smem4 + team_floats(sp.nsr, P * H, H) / 4);
+  float* atab = reinterpret_cast<float*>(dh + dh_stride(sp));
+  float4* cols = reinterpret_cast<float4*>(atab + atab_stride(g));
+  ChainState* cs0 = reinterpret_cast<ChainState*>(cols + sp.P * 64);
+  float2* wt = reinterpret_cast<float2*>(cs0 + T * H) + quad_table_len(g, sp) * ch;
+  ChainState* cs = cs0 + wave * H + ch;
+  build_col_table(g, sp, cols);
+  stage_galaxy(a, gal, g, sp, dh, nullptr, atab);
+  // the 64-word record of this lane's chain, copied by the chain's lanes
+  const int64_t chain = (int64_t)gal * a.C + cw;
+  uint32_t* csw = reinterpret_cast<uint32_t*>(cs);
+  uint32_t* st = reinterpret_cast<uint32_t*>(a.state + chain);
+  const int cl = chain_lane<H>();
+#pragma unroll
+  for (int k = 0; k < H; ++k) csw[cl + (kWave / H) * k] = st[cl + (kWave / H) * k];
+  __syncthreads();
+  const Prior pr{a.lf_lo, a.lf_hi, a.ls_lo, a.ls_hi, a.sigma_d, a.sigma_e,
+                 1.0f / (a.sigma_d * a.sigma_d), 1.0f / (a.sigma_e * a.sigma_e)};
+  const float sig = a.sigma[gal];
+  GalCtx c;
+  c.g = g;
+  c.sp = sp;
+  c.dh = dh;
+  c.atab = atab;
+  c.Ym = reinterpret_cast<float4*>(wt);
+  c.X = wt + 2 * sp.ymax;
+  c.Yf = nullptr;
+  c.cols = cols;
+  c.part = wave;
+  c.team = carve_team<P * H, H>(reinterpret_cast<float*>(smem4), sp.nsr, wave);
+  c.norm = 1.0f / ((float)g.N * (float)g.N * sig * sig);
+  c.rscale = a.rscale;
+  c.nu = a.nu;
+  c.refx = a.ref_xy[2 * (int64_t)gal];
+  c.refy = a.ref_xy[2 * (int64_t)gal + 1];
+  c.t_stop = a.t_stop_gal ? min(a.t_stop, a.t_stop_gal[gal]) : a.t_stop;
+  const auto tc = team_cols<NFIX, P, H>(cols, atab, g, wave);
+  fill_team_zeros<H>(g, sp, c.X, c.Ym);
+  // the T waves hold identical copies of the chains' state; the first writes
+  // the outputs
+  float* sc = (a.samples && wave == 0) ? a.samples + chain * (int64_t)a.S * 6 : nullptr;
+  float* tr = (a.trace && wave == 0) ? a.trace + chain * (int64_t)a.t_stop * 4 : nullptr;
+  advance_chain<PROF, P, NFIX, 1, H>(a, c, tc, pr, cs, sc, tr);
+  if (wave == 0)
+#pragma unroll
+    for (int k = 0; k < H; ++k) st[cl + (kWave / H) * k] = csw[cl + (kWave / H) * k];
+}
+
 __global__ void hmc_finalize_kernel(const ChainState* __restrict__ st, int n_gal, int C, int S,
                                     float* __restrict__ stats, uint32_t* __restrict__ status) {
   const int gal = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1548,6 +1635,53 @@ static bool launch_fixed_nuts(const HmcArgs& a, int grid, size_t lds, hipStream_
   return false;
 }
 
+// Team kernels: the default plans of the odd specialised sides, in the forms
+// whose lane columns split (team_waves).
+constexpr bool team_plan(int N, int P, int H) {
+  return (N & 1) && P == make_slot_plan(N).P && team_waves(P * H) > 1 &&
+         (H == 1 || paired_chains_plan(N, P)) && (H < 4 || quad_chains_plan(N, P));
+}
+
+// A team holds its chains' place on a compute unit with T waves instead of
+// one, so it is the shorter way only while all groups are resident at once:
+// with two waves a SIMD (the kernel's registers) and the LDS, 512 groups of
+// three or four waves or 1,024 of two on 256 compute units.  20 iterations of
+// 20 steps at C = 4 and 53 px: 1 galaxy 1.03 ms (one wave a group 2.39), 256
+// 1.17 (2.44), 512 1.32 (2.50), 768 2.28 (2.24); at C = 1: 53 px 0.63 (1.02), 0.68
+// (1.03), 0.75 (1.08), 768 1.44 (0.85); 101 px 1 galaxy 0.98 (2.09), 256 1.03
+// (2.12), 512 1.33 (2.30).
+constexpr int team_groups(int N, int P, int H) {
+  const int waves = 4 * kHmcWavesPerEu / team_waves(P * H), lds = (int)(160 * 1024 / team_lds_bytes(N, P, H));
+  return 256 * (waves < lds ? waves : lds);
+}
+
+template <int PROF, int NN, int PP, int H>
+static bool launch_team_h(const HmcArgs& a, hipStream_t s) {
+  if constexpr (team_plan(NN, PP, H)) {
+    constexpr size_t lds = team_lds_bytes(NN, PP, H);
+    static_assert(team_groups(NN, PP, H) > 0, "team: beyond a compute unit's LDS");
+    if ((int64_t)std::max(a.n_gal, a.n_side) * (a.C / H) > team_groups(NN, PP, H)) return false;
+    auto k = hmc_team_kernel<PROF, PP, NN, H>;
+    (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(k, dim3(a.n_gal * (a.C / H)), dim3(kWave * team_waves(PP * H)), lds, s, a);
+    return true;
+  }
+  return false;
+}
+
+template <int PROF>
+static bool launch_team(const HmcArgs& a, int H, hipStream_t s) {
+#define BSI_CASE(NN, PP)                                                   \
+  if (a.N == NN && a.P == PP) {                                            \
+    if (H == 4) return launch_team_h<PROF, NN, PP, 4>(a, s);               \
+    if (H == 2) return launch_team_h<PROF, NN, PP, 2>(a, s);               \
+    return launch_team_h<PROF, NN, PP, 1>(a, s);                           \
+  }
+  BSI_FIXED_PLANS(BSI_CASE)
+#undef BSI_CASE
+  return false;
+}
+
 template <int PROF, bool INIT>
 static void launch_prof(const HmcArgs& a, int grid, size_t lds, hipStream_t s) {
   if constexpr (!INIT && PROF != kProfGauss)
@@ -1609,6 +1743,10 @@ static hipError_t launch_impl(const HmcArgs& a, int grid, hipStream_t s) {
   // several chains per wave exactly where launch_fixed_w, launch_fixed_nuts
   // and launch_fixed_mx launch them
   const int H = launch_chains_per_wave(a, INIT);
+  // teams (single steps stay with the plain kernels: staging would dominate)
+  if (!INIT && !a.nuts && !a.mx && a.wpc == 1 && a.n_steps > 1 && a.prof != kProfGauss &&
+      (a.prof == kProfExp ? launch_team<kProfExp>(a, H, s) : launch_team<kProfSpergel>(a, H, s)))
+    return hipGetLastError();
   const size_t lds = a.mx ? hmc_lds_bytes(a.N, a.C, a.P, 1, H, a.n_exp, true, a.nuts)
                           : hmc_lds_bytes(a.N, a.C, a.P, INIT ? 1 : a.wpc, H, 1, false, a.nuts);
   if (a.prof == kProfExp)

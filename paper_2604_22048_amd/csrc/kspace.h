@@ -334,11 +334,18 @@ __device__ __forceinline__ void fill_tables(const Geom& g, const SlotPlan& sp,
 // data spectrum is stored whitened (D sqrt w) and sw = (sqrt w(+kx), sqrt
 // w(-kx)) scales the model of each bin, so every sum above becomes its
 // w-weighted form (Appendix C, eq. covar-pixel-likelihood).
+//
+// pair_terms adds a pair to its column's sums and returns what the sums that
+// run over all columns take from it: the residuals R (sum |R|^2), ws (times
+// ky^2) and gz (times ky).
+struct PairTerms {
+  float Rpr, Rpi, Rmr, Rmi, ws, gz;
+};
+
 template <int PROF, bool RESID, bool CORR = false>
-__device__ __forceinline__ void pair_step(const Shape& sh, float4 D, float4 y, float xr, float xi,
-                                          float TA, float Tc, float& c2, float& swq,
-                                          float& syy, float& wky, float& sdx, float& sdy, bool chi2,
-                                          float2 sw = float2{1.f, 1.f}) {
+__device__ __forceinline__ PairTerms pair_terms(const Shape& sh, float4 D, float4 y, float xr, float xi,
+                                                float TA, float Tc, float& swq, float& wky, float& sdx,
+                                                float2 sw = float2{1.f, 1.f}) {
   const float base = fmaf(sh.tb, y.w, TA);
   const float tp = fmaf(Tc, y.z, base), tm = fmaf(-Tc, y.z, base);
   float Gp, Gm, Gwp, Gwm;
@@ -371,17 +378,30 @@ __device__ __forceinline__ void pair_step(const Shape& sh, float4 D, float4 y, f
   const float Rpi = RESID ? D.y : fmaf(-Gp, ppi, D.y);
   const float Rmr = RESID ? D.z : fmaf(-Gm, pmr, D.z);
   const float Rmi = RESID ? D.w : fmaf(-Gm, pmi, D.w);
-  if (chi2) c2 = fmaf(Rpr, Rpr, fmaf(Rpi, Rpi, fmaf(Rmr, Rmr, fmaf(Rmi, Rmi, c2))));
   const float zrp = fmaf(Rpr, ppr, Rpi * ppi), zip = fmaf(Rpr, ppi, -Rpi * ppr);
   const float zrm = fmaf(Rmr, pmr, Rmi * pmi), zim = fmaf(Rmr, pmi, -Rmi * pmr);
   const float wqp = Gwp * zrp;
   const float ws = fmaf(Gwm, zrm, wqp), wd = fmaf(-Gwm, zrm, wqp);
   swq += ws;
-  syy = fmaf(y.w, ws, syy);
   wky = fmaf(y.z, wd, wky);
   const float gzp = Gp * zip;
-  sdx = fmaf(-Gm, zim, sdx + gzp);
-  sdy = fmaf(y.z, fmaf(Gm, zim, gzp), sdy);
+  sdx = fmaf(-Gm, zim, fmaf(Gp, zip, sdx));
+  return PairTerms{Rpr, Rpi, Rmr, Rmi, ws, fmaf(Gm, zim, gzp)};
+}
+
+__device__ __forceinline__ float pair_chi2(float Rpr, float Rpi, float Rmr, float Rmi, float c2) {
+  return fmaf(Rpr, Rpr, fmaf(Rpi, Rpi, fmaf(Rmr, Rmr, fmaf(Rmi, Rmi, c2))));
+}
+
+template <int PROF, bool RESID, bool CORR = false>
+__device__ __forceinline__ void pair_step(const Shape& sh, float4 D, float4 y, float xr, float xi,
+                                          float TA, float Tc, float& c2, float& swq,
+                                          float& syy, float& wky, float& sdx, float& sdy, bool chi2,
+                                          float2 sw = float2{1.f, 1.f}) {
+  const PairTerms t = pair_terms<PROF, RESID, CORR>(sh, D, y, xr, xi, TA, Tc, swq, wky, sdx, sw);
+  if (chi2) c2 = pair_chi2(t.Rpr, t.Rpi, t.Rmr, t.Rmi, c2);
+  syy = fmaf(y.w, t.ws, syy);
+  sdy = fmaf(y.z, t.gz, sdy);
 }
 
 // Split evaluation (W > 1 waves per chain, NFIX kernels only): wave `part`
@@ -689,6 +709,306 @@ __device__ KSums kspace_sums_blocked(const float4* cols, const float2* __restric
   float v[7] = {w0, sxx, syy, sxy, sdx, sdy, 0.f};
   s.chi2 = CHI2 ? group_total<H>(chi2) : 0.0;
   group_total7<H>(v, red);
+  s.sF = v[0];
+  s.sxx = v[1];
+  s.syy = v[2];
+  s.sxy = v[3];
+  s.sdx = v[4];
+  s.sdy = v[5];
+  s.sq = sh.ca * s.sxx + sh.cb * s.syy + sh.cc * s.sxy;
+  s.sF = flux_sum<PROF>(s.sF, s.sq, sh);
+  return s;
+}
+
+// ---- Team evaluation: T waves per group of H chains ------------------------
+//
+// Small launches leave most of the chip idle while each chain group's wave
+// works through its pair loop alone.  A team's T waves (one workgroup) share
+// one evaluation: wave w takes the lane's columns w NC .. w NC + NC - 1 of
+// every super-row.  The totals are those of kspace_sums and
+// kspace_sums_blocked to the last bit: a column's own sums run over the
+// super-rows within its wave, in the order of those loops, and the sums that
+// run over all columns (ky^2, ky and |R|^2) are taken from the pairs' terms in
+// LDS in exactly their order, each by one wave; the column sums are folded in
+// column order by another.  Every wave then finishes the reduction for
+// itself, so the T waves hold identical chain states and none waits for
+// another's result beyond the three barriers of an evaluation (tables filled,
+// terms written, lane sums written).
+
+// Waves of a team for PI columns per lane: a divisor of PI, at most the four
+// SIMDs of a compute unit; 1 if PI does not split.
+constexpr int team_waves(int PI) { return PI % 4 == 0 ? 4 : PI % 3 == 0 ? 3 : PI % 2 == 0 ? 2 : 1; }
+
+// Pair b in the order of the plain loops (by block, super-row, column), as its
+// place k PI + i in the term tables.
+constexpr int team_slot(int b, int K, int PI, int CB) {
+  return b / CB % K * PI + b / (CB * K) * CB + b % CB;
+}
+
+struct TeamLds {
+  float* term;     // ws, then gz of each pair [2][nsr PI][64]
+  float* col;      // column sums [3][PI][64]; before them |R|^2 by column
+                   // block and super-row [PI / CB][nsr][64]
+  float* red;      // lane sums [64][8]
+  float* own;      // this wave's reduction scratch (32 floats)
+  double* chi2;    // per chain of the group
+};
+
+// Columns per block in the order of the plain loops: kspace_sums_blocked with
+// four chains per wave, else all of them.
+constexpr int team_block(int PI, int H) { return H == 4 && PI > 6 ? 6 : PI; }
+
+// LDS of the above, in floats (all pieces 16-byte multiples).
+__host__ __device__ constexpr int team_floats(int nsr, int PI, int H) {
+  const int c2 = nsr * (PI / team_block(PI, H));
+  return 64 * (2 * nsr * PI + (c2 > 3 * PI ? c2 : 3 * PI)) + 512 + 32 * team_waves(PI) + 8;
+}
+
+template <int PI, int H>
+__device__ __forceinline__ TeamLds carve_team(float* at, int nsr, int part) {
+  TeamLds l;
+  l.term = at;
+  l.col = l.term + 128 * nsr * PI;
+  l.red = at + team_floats(nsr, PI, H) - (512 + 32 * team_waves(PI) + 8);
+  l.own = l.red + 512 + 32 * part;
+  l.chi2 = reinterpret_cast<double*>(l.red + 512 + 32 * team_waves(PI));
+  return l;
+}
+
+// What a lane of a team keeps in registers over a whole trajectory: its wave's
+// columns, the row factors of the sum the wave chains (part 0: ky^2, else ky)
+// and the lane's entry of its chain's tables (fill_team).
+template <int NFIX, int P, int H>
+struct TeamCols {
+  static constexpr int PI = P * H, T = team_waves(PI), NC = PI / T, K = make_slot_plan_p(NFIX, P).nsr;
+  float kx[NC], kx2[NC];
+  int xi[NC], yo[NC];
+  float yk[K * PI];
+  int fx, fy;            // entry of X (u = fx) or of Ym (row fy); -1: none
+  float fk, fa, fky;     // u or v, a(u) or a(v), k_v
+};
+
+template <int NFIX, int P, int H>
+__device__ __forceinline__ TeamCols<NFIX, P, H> team_cols(const float4* cols, const float* atab, const Geom& g,
+                                                          int part) {
+  using TC = TeamCols<NFIX, P, H>;
+  constexpr int LS = kWave / H, R = make_slot_plan_p(NFIX, P).R;
+  TC c;
+  const int lane = chain_lane<H>();
+#pragma unroll
+  for (int j = 0; j < TC::NC; ++j) {
+    const float4 e = cols[lane + LS * (part * TC::NC + j)];
+    c.kx[j] = e.x;
+    c.kx2[j] = e.y;
+    c.xi[j] = __float_as_int(e.z);
+    c.yo[j] = __float_as_int(e.w);
+  }
+#pragma unroll
+  for (int i = 0; i < TC::PI; ++i) {
+    const int yo = __float_as_int(cols[lane + LS * i].w);
+#pragma unroll
+    for (int k = 0; k < TC::K; ++k) {
+      const int v = yo + k * R;
+      const float ky = v <= g.hc ? (float)v * g.kstep : 0.f;
+      c.yk[k * TC::PI + i] = part == 0 ? ky * ky : ky;
+    }
+  }
+  // X's entries u = 0..hc come first, then Ym's rows 0..hc, one a lane
+  static_assert(NFIX + 1 <= TC::T * LS, "one table entry a lane");
+  const int t = part * LS + lane, v = t - (g.hc + 1);
+  c.fx = v < 0 ? t : -1;
+  c.fy = v >= 0 && v <= g.hc ? v : -1;
+  c.fk = (float)(v < 0 ? t : v);
+  const float at = atab[c.fx >= 0 ? c.fx + g.h : c.fy >= 0 ? c.fy + g.h : g.h];
+  c.fa = c.fy == 0 ? at * 0.70710678118654752f : at;
+  c.fky = (float)v * g.kstep;
+  return c;
+}
+
+// The tables of fill_tables (odd N), each entry by one lane of the team; the
+// zero entries (X[ntab], rows past hc) are written once by fill_team_zeros.
+template <int NFIX, int P, int H>
+__device__ __forceinline__ void fill_team(const TeamCols<NFIX, P, H>& c, const Geom& g, float2* X, float4* Ym,
+                                          float F, float dx, float dy) {
+  const float r = (c.fx >= 0 ? dx : dy) * rcp_nr((float)g.N);
+  const float2 w = cis_neg_rev(c.fk * r);
+  if (c.fx >= 0) {
+    const float a = F * c.fa;
+    X[c.fx + g.h] = make_float2(a * w.x, a * w.y);
+    if (c.fx == 0) X[g.ntab + 1] = make_float2(0.70710678118654752f * a * w.x, 0.70710678118654752f * a * w.y);
+  }
+  if (c.fy >= 0) Ym[c.fy] = make_float4(c.fa * w.x, c.fa * w.y, c.fky, c.fky * c.fky);
+  __syncthreads();
+}
+
+template <int H>
+__device__ __forceinline__ void fill_team_zeros(const Geom& g, const SlotPlan& sp, float2* X, float4* Ym) {
+  const int lane = chain_lane<H>();
+  if (lane == 0) X[g.ntab] = make_float2(0.f, 0.f);
+  for (int v = g.hc + 1 + lane; v < sp.ymax; v += kWave / H) Ym[v] = make_float4(0.f, 0.f, 0.f, 0.f);
+}
+
+template <int PROF, int P, bool CHI2, int NFIX, int H>
+__device__ __forceinline__ KSums kspace_sums_team(const TeamCols<NFIX, P, H>& tc, const float4* cols,
+                                                  const float2* __restrict__ dh, const float2* X,
+                                                  const float4* Ym, const Shape& sh, const TeamLds& l,
+                                                  int part) {
+  using TC = TeamCols<NFIX, P, H>;
+  constexpr SlotPlan spc = make_slot_plan_p(NFIX, P);
+  constexpr int LS = kWave / H, PI = TC::PI, T = TC::T, NC = TC::NC, K = TC::K;
+  // the order of the plain loops: by block of CB columns, within it by super-row
+  constexpr int CB = team_block(PI, H);
+  static_assert((NFIX & 1) && PI % CB == 0 && CB % NC == 0, "odd stamp sides, whole column blocks");
+  const int lane = chain_lane<H>(), wl = lane_id();
+  const int c0 = part * NC;
+  double chi2 = 0.0;
+  {
+    float xr[NC], xi[NC], TA[NC], Tc[NC], swq[NC], wky[NC], sdc[NC];
+    const float4* yq[NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const float2 x = X[tc.xi[j]];
+      xr[j] = x.x;
+      xi[j] = x.y;
+      TA[j] = fmaf(sh.ta, tc.kx2[j], sh.t0);
+      Tc[j] = sh.tc * tc.kx[j];
+      yq[j] = Ym + tc.yo[j];
+      swq[j] = 0.f;
+      wky[j] = 0.f;
+      sdc[j] = 0.f;
+    }
+    const float4* dp = reinterpret_cast<const float4*>(dh) + lane + LS * c0;
+    float* tp = l.term + 64 * c0 + wl;
+    if constexpr (!CHI2) {
+      float4 Dn = dp[0];
+      float4 yn = yq[0][0];
+#pragma unroll
+      for (int b = 0; b < K * NC; ++b) {
+        const int k = b / NC, j = b % NC;
+        const float4 D = Dn;
+        const float4 y = yn;
+        if (b + 1 < K * NC) {
+          Dn = dp[((b + 1) / NC * PI + (b + 1) % NC) * LS];
+          yn = yq[(b + 1) % NC][(b + 1) / NC * spc.R];
+        }
+        __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of this pair's arithmetic
+        const PairTerms t =
+            pair_terms<PROF, false>(sh, D, y, xr[j], xi[j], TA[j], Tc[j], swq[j], wky[j], sdc[j]);
+        tp[64 * (k * PI + j)] = t.ws;
+        tp[64 * (K * PI + k * PI + j)] = t.gz;
+      }
+    } else {
+      // |R|^2 of a super-row runs over a block's columns: the waves that hold
+      // them take the super-row one after another, each adding to the sum of
+      // the one before (once a trajectory)
+      float* c2p = l.col + 64 * K * (c0 / CB) + wl;
+      const int turn = c0 % CB / NC;
+#pragma unroll 1
+      for (int r = 0; r < K + CB / NC - 1; ++r) {
+        const int k = r - turn;
+        if (k >= 0 && k < K) {
+          float c2 = turn > 0 ? c2p[64 * k] : 0.f;
+#pragma unroll
+          for (int j = 0; j < NC; ++j) {
+            const PairTerms t = pair_terms<PROF, false>(sh, dp[(k * PI + j) * LS], yq[j][k * spc.R], xr[j],
+                                                        xi[j], TA[j], Tc[j], swq[j], wky[j], sdc[j]);
+            tp[64 * (k * PI + j)] = t.ws;
+            tp[64 * (K * PI + k * PI + j)] = t.gz;
+            c2 = pair_chi2(t.Rpr, t.Rpi, t.Rmr, t.Rmi, c2);
+          }
+          c2p[64 * k] = c2;
+        }
+        __syncthreads();
+      }
+      if (part == T - 1)
+#pragma unroll
+        for (int k = 0; k < K * (PI / CB); ++k) chi2 += (double)l.col[64 * k + wl];
+      __syncthreads();
+    }
+    float* cp = l.col + 64 * c0 + wl;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      cp[64 * j] = swq[j];
+      cp[64 * (PI + j)] = wky[j];
+      cp[64 * (2 * PI + j)] = sdc[j];
+    }
+  }
+  __syncthreads();
+  // each sum over all columns by one wave: ky^2 (part 0) and ky (part 1) from
+  // the pairs' terms, the rest by the team's other waves
+  // (the reads go out in batches ahead of the adds: left to the compiler, each
+  // pair of adds waits for its own read, 3.1 us an evaluation at 101 px and one
+  // chain instead of 2.5)
+  if (part < 2) {
+    const float* tp = l.term + 64 * (K * PI) * part + wl;
+    constexpr int NB = 24;
+    float s = 0.f;
+#pragma unroll
+    for (int b0 = 0; b0 < K * PI; b0 += NB) {
+      float t[NB];
+#pragma unroll
+      for (int b = b0; b < b0 + NB && b < K * PI; ++b) t[b - b0] = tp[64 * team_slot(b, K, PI, CB)];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int b = b0; b < b0 + NB && b < K * PI; ++b) {
+        const int x = team_slot(b, K, PI, CB);
+        if (pair_iter_live(NFIX, spc, LS, x / PI, x % PI)) s = fmaf(tc.yk[x], t[b - b0], s);
+      }
+    }
+    l.red[8 * wl + (part == 0 ? 2 : 5)] = s;
+  }
+  if (part == (T > 2 ? 2 : 0)) {
+    const float* cp = l.col + wl;
+    float q[PI], kx2[PI];
+#pragma unroll
+    for (int i = 0; i < PI; ++i) {
+      q[i] = cp[64 * i];
+      kx2[i] = cols[lane + LS * i].y;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    float w0 = 0.f, sxx = 0.f;
+#pragma unroll
+    for (int i = 0; i < PI; ++i) {
+      w0 += q[i];
+      sxx = fmaf(kx2[i], q[i], sxx);
+    }
+    l.red[8 * wl] = w0;
+    l.red[8 * wl + 1] = sxx;
+  }
+  if (part == T - 1) {
+    const float* cp = l.col + 64 * PI + wl;
+    float wk[PI], sd[PI], kx[PI];
+#pragma unroll
+    for (int i = 0; i < PI; ++i) {
+      wk[i] = cp[64 * i];
+      sd[i] = cp[64 * (PI + i)];
+      kx[i] = cols[lane + LS * i].x;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    float sxy = 0.f, sdx = 0.f;
+#pragma unroll
+    for (int i = 0; i < PI; ++i) {
+      sxy = fmaf(kx[i], wk[i], sxy);
+      sdx = fmaf(kx[i], sd[i], sdx);
+    }
+    l.red[8 * wl + 3] = sxy;
+    l.red[8 * wl + 4] = sdx;
+  }
+  if (CHI2 && part == T - 1) {
+    if constexpr (H == 1)
+      chi2 = wave_total(chi2);
+    else
+      chi2 = group_total<H>(chi2);
+    if (lane == 0) l.chi2[wl / LS] = chi2;
+  }
+  __syncthreads();
+  KSums s;
+  float v[7];
+  if constexpr (H == 1)
+    wave_gather7(v, l.red);
+  else
+    group_gather7<H>(v, l.red, l.own);
+  s.chi2 = CHI2 ? l.chi2[wl / LS] : 0.0;
   s.sF = v[0];
   s.sxx = v[1];
   s.syy = v[2];

@@ -495,7 +495,8 @@ int bsi_slots_advance(bsi_slots sv, int32_t n_iter) {
         iters[i] = (int)std::min<double>(64.0 * n_iter, std::max(1.0, std::round(n_iter * tmax / tau)));
     }
   }
-  const HmcArgs base = base_args(sv);
+  HmcArgs base = base_args(sv);
+  for (int i : active) base.n_side += (int)sv->cls[i].resident.size();
   e = fork_join(h, sv->s, (int)active.size(), [&](int j, hipStream_t st) -> hipError_t {
     const int i = active[j];
     const SizeClass& k = sv->cls[i];
