@@ -196,17 +196,21 @@ hipError_t class_spectrum(bsi_handle h, const Plan& p, const ClassRange& c, cons
 // forked streams, or under capture in sequence on s (capturing the fork/join
 // has ended in a host segmentation fault inside the call, cause not
 // identified, so it is never captured).
-template <typename F>
-hipError_t for_classes(bsi_handle h, const Plan& p, hipStream_t s, bool cap, F&& fn) {
+// cost(class) estimates a class's duration: by default its share of the work.
+template <typename F, typename Cost>
+hipError_t for_classes(bsi_handle h, const Plan& p, hipStream_t s, bool cap, F&& fn, Cost&& cost) {
   const int n = (int)p.classes.size();
   if (!cap)
-    return fork_join(h, s, n, [&](int i, hipStream_t st) { return fn(p.classes[i], st); }, [&](int i) {
-      const ClassRange& c = p.classes[i];
-      return (double)c.N * c.N * c.gcount;    // the class's share of the work
-    });
+    return fork_join(h, s, n, [&](int i, hipStream_t st) { return fn(p.classes[i], st); },
+                     [&](int i) { return cost(p.classes[i]); });
   hipError_t e = hipSuccess;
   for (int i = 0; e == hipSuccess && i < n; ++i) e = fn(p.classes[i], s);
   return e;
+}
+
+template <typename F>
+hipError_t for_classes(bsi_handle h, const Plan& p, hipStream_t s, bool cap, F&& fn) {
+  return for_classes(h, p, s, cap, fn, [](const ClassRange& c) { return (double)c.N * c.N * c.gcount; });
 }
 
 // Leapfrog evaluations of a chain per launch, about: a launch costs 6 us plus
@@ -588,7 +592,13 @@ int bsi_hmc_sample(bsi_handle h, const bsi_batch* batch, const float* data, cons
   a.off = static_cast<const int64_t*>(h->off.p);
   a.nuts = nuts ? 1 : 0;
   a.max_depth = cfg->max_tree_depth;
-  a.n_side = batch->n_gal;
+  for (const ClassRange& c : p.classes) {
+    HmcArgs ac = a;
+    ac.N = c.N;
+    ac.P = c.P;
+    ac.n_gal = c.gcount;
+    a.side_waves += hmc_team_waves(ac);
+  }
 
   const int T = a.t_stop;
   const bool plain = cfg->form == BSI_FORM_PLAIN;
@@ -623,7 +633,7 @@ int bsi_hmc_sample(bsi_handle h, const bsi_batch* batch, const float* data, cons
       x = launch_hmc_advance(ac, c.gcount, st);
     }
     return x;
-  });
+  }, [](const ClassRange& c) { return chain_cost(c.N) * std::max(1.0, c.gcount / 512.0); });
   if (e != hipSuccess) return hip_fail(h, e, "hmc launch");
   e = launch_hmc_finalize(static_cast<const ChainState*>(h->state.p), batch->n_gal, C, cfg->n_samples,
                           chain_stats, status, s);

@@ -130,7 +130,6 @@ struct HmcArgs {
   const int64_t* bin_off;
   const int32_t* gidx;
   int n_gal;              // galaxies in this launch (entries of gidx)
-  int n_side;             // galaxies of all launches that run side by side with it (0: this one alone)
   const float* psf;
   const float* sigma;
   const float* ref_xy;
@@ -164,6 +163,9 @@ struct HmcArgs {
   const int64_t* off;
   // NUTS (one wave or half-wave per chain): n_steps counts transitions
   int nuts, max_depth;
+  // hmc_team_waves over all launches that run side by side with this one
+  // (advance kernels; 0: this one alone)
+  int64_t side_waves;
 };
 
 // Deepest NUTS tree (doublings per transition).
@@ -181,6 +183,9 @@ int hmc_split_waves(int N, int C, int P, int prof, int max_w);
 // Whether the advance kernel with exposures / noise weights (mx) runs on the
 // kernels specialised for stamp side N: one wave per chain, the exponential or
 // Spergel profile and P N's default plan with a specialised kernel.
+// Waves of an advance launch if its chain groups are evaluated by teams, where
+// there is a team kernel (a.side_waves decides whether they are).
+int64_t hmc_team_waves(const HmcArgs& a);
 bool hmc_mx_fixed(int N, int P, int prof, int wpc);
 // Slot plans with a trajectory kernel specialised for stamp side N (0-terminated list of P).
 const int* hmc_fixed_plans(int N);

@@ -150,7 +150,7 @@ __device__ __forceinline__ double potential(const GalCtx& c, const Cols& lc, con
     fill_team(lc, c.g, c.X, c.Ym, F, dx, dy);
     const KSums S =
         kspace_sums_team<PROF, P, CHI2, NFIX, H>(lc, c.cols, c.dh, c.X, c.Ym, sh, c.team, c.part);
-    r = kspace_finish<PROF>(S, sh, F, s, e1, e2, c.norm);
+    r = kspace_finish<PROF, true>(S, sh, F, s, e1, e2, c.norm);
   } else {
     fill_tables<H>(c.g, c.sp, c.atab, c.X, c.Ym, c.Yf, F, dx, dy);
     KSums S;
@@ -716,8 +716,8 @@ __device__ __forceinline__ bool u_turn(const float* pa, const float* pb, const f
 }
 
 // Advance the chain by up to a.n_steps NUTS transitions (iterations).
-template <int PROF, int P, int NFIX, bool MX>
-__device__ void advance_chain_nuts(const HmcArgs& a, const GalCtx& c, const LaneCols<P>& lc,
+template <int PROF, int P, int NFIX, bool MX, class Cols = LaneCols<P>>
+__device__ void advance_chain_nuts(const HmcArgs& a, const GalCtx& c, const Cols& lc,
                                    const Prior& pr, ChainState* cs, NutsTree* tr,
                                    float* samples_chain, float* trace_chain) {
   const int lane = lane_id();
@@ -942,8 +942,8 @@ __device__ void advance_chain_nuts(const HmcArgs& a, const GalCtx& c, const Lane
 // whose transitions are done evaluates at its last position and discards the
 // result until the other half is done too.  The trees and the random streams
 // are those of advance_chain_nuts, so both forms give the same chains.
-template <int PROF, int P, int NFIX>
-__device__ void advance_chain_nuts2(const HmcArgs& a, const GalCtx& c, const LaneCols<2 * P>& lc,
+template <int PROF, int P, int NFIX, class Cols = LaneCols<2 * P>>
+__device__ void advance_chain_nuts2(const HmcArgs& a, const GalCtx& c, const Cols& lc,
                                     const Prior& pr, ChainState* cs, NutsTree* tr,
                                     float* samples_chain, float* trace_chain) {
   constexpr int H = 2;
@@ -1320,25 +1320,25 @@ __global__ void __launch_bounds__(MAXT, (MAXT > 256 ? 1 : kHmcWavesPerEu)) hmc_k
 // ---- Trajectories by teams ---------------------------------------------------
 
 // LDS: [team exchange areas | data spectrum | atab | column table | T H chain
-// records | H table sets without the Nyquist table].
-constexpr size_t team_lds_bytes(int N, int P, int H) {
+// records | H table sets without the Nyquist table | NUTS: T H trees].
+constexpr size_t team_lds_bytes(int N, int P, int H, bool nuts) {
   const Geom g = make_geom(N);
   const SlotPlan sp = make_slot_plan_p(N, P);
   const int T = team_waves(P * H);
-  return sizeof(float) * team_floats(sp.nsr, P * H, H) + sizeof(float2) * dh_stride(sp) +
+  return sizeof(float) * team_floats(sp.nsr, P * H, H, nuts) + sizeof(float2) * dh_stride(sp) +
          sizeof(float) * atab_stride(g) + sizeof(float4) * sp.P * 64 + sizeof(ChainState) * T * H +
-         sizeof(float2) * quad_table_len(g, sp) * H;
+         sizeof(float2) * quad_table_len(g, sp) * H + (nuts ? sizeof(NutsTree) * T * H : 0);
 }
 
 // One workgroup of T waves per group of H chains (the chains that share a wave
-// in hmc_kernel): fixed-length trajectories, one exposure, odd stamp sides.
-// For launches with fewer chain groups than the chip has SIMDs: an evaluation
+// in hmc_kernel): one exposure, odd stamp sides.  For launches with fewer chain groups than the chip has SIMDs: an evaluation
 // of four chains at 53 px takes one wave 5.3 us, most of it the wave's own
 // instruction issue; a team's 2.6 us are the longest wave's issue (12 pairs of 42
 // instructions at 4 cycles, 0.85 us), the serial part that every wave repeats and
 // the three barriers.
-template <int PROF, int P, int NFIX, int H>
+template <int PROF, int P, int NFIX, int H, bool NUTS>
 __global__ void __launch_bounds__(kWave * team_waves(P * H), kHmcWavesPerEu) hmc_team_kernel(HmcArgs a) {
+  static_assert(!NUTS || H <= 2, "NUTS: one or two chains per wave");
   constexpr int T = team_waves(P * H);
   constexpr Geom g = make_geom(NFIX);
   constexpr SlotPlan sp = make_slot_plan_p(NFIX, P);
@@ -1348,11 +1348,12 @@ __global__ void __launch_bounds__(kWave * team_waves(P * H), kHmcWavesPerEu) hmc
   const int gal = a.gidx[blockIdx.x / groups];
   const int ch = lane_id() / (kWave / H);                    // chain within the group
   const int cw = (int)(blockIdx.x % groups) * H + ch;        // chain of the galaxy
-  float2* dh = reinterpret_cast<float2*>(smem4 + team_floats(sp.nsr, P * H, H) / 4);
+  float2* dh = reinterpret_cast<float2*>(smem4 + team_floats(sp.nsr, P * H, H, NUTS) / 4);
   float* atab = reinterpret_cast<float*>(dh + dh_stride(sp));
   float4* cols = reinterpret_cast<float4*>(atab + atab_stride(g));
   ChainState* cs0 = reinterpret_cast<ChainState*>(cols + sp.P * 64);
-  float2* wt = reinterpret_cast<float2*>(cs0 + T * H) + quad_table_len(g, sp) * ch;
+  float2* wt0 = reinterpret_cast<float2*>(cs0 + T * H);
+  float2* wt = wt0 + quad_table_len(g, sp) * ch;
   ChainState* cs = cs0 + wave * H + ch;
   build_col_table(g, sp, cols);
   stage_galaxy(a, gal, g, sp, dh, nullptr, atab);
@@ -1377,20 +1378,28 @@ __global__ void __launch_bounds__(kWave * team_waves(P * H), kHmcWavesPerEu) hmc
   c.Yf = nullptr;
   c.cols = cols;
   c.part = wave;
-  c.team = carve_team<P * H, H>(reinterpret_cast<float*>(smem4), sp.nsr, wave);
+  c.team = carve_team<P * H, H, NUTS>(reinterpret_cast<float*>(smem4), sp.nsr, wave);
   c.norm = 1.0f / ((float)g.N * (float)g.N * sig * sig);
   c.rscale = a.rscale;
   c.nu = a.nu;
   c.refx = a.ref_xy[2 * (int64_t)gal];
   c.refy = a.ref_xy[2 * (int64_t)gal + 1];
   c.t_stop = a.t_stop_gal ? min(a.t_stop, a.t_stop_gal[gal]) : a.t_stop;
-  const auto tc = team_cols<NFIX, P, H>(cols, atab, g, wave);
+  const auto tc = team_cols<NFIX, P, H, NUTS>(cols, atab, g, wave);
   fill_team_zeros<H>(g, sp, c.X, c.Ym);
   // the T waves hold identical copies of the chains' state; the first writes
   // the outputs
   float* sc = (a.samples && wave == 0) ? a.samples + chain * (int64_t)a.S * 6 : nullptr;
   float* tr = (a.trace && wave == 0) ? a.trace + chain * (int64_t)a.t_stop * 4 : nullptr;
-  advance_chain<PROF, P, NFIX, 1, H>(a, c, tc, pr, cs, sc, tr);
+  if constexpr (NUTS) {
+    NutsTree* tree = reinterpret_cast<NutsTree*>(wt0 + quad_table_len(g, sp) * H) + wave * H + ch;
+    if constexpr (H == 2)
+      advance_chain_nuts2<PROF, P, NFIX>(a, c, tc, pr, cs, tree, sc, tr);
+    else
+      advance_chain_nuts<PROF, P, NFIX, false>(a, c, tc, pr, cs, tree, sc, tr);
+  } else {
+    advance_chain<PROF, P, NFIX, 1, H>(a, c, tc, pr, cs, sc, tr);
+  }
   if (wave == 0)
 #pragma unroll
     for (int k = 0; k < H; ++k) st[cl + (kWave / H) * k] = csw[cl + (kWave / H) * k];
@@ -1636,10 +1645,14 @@ static bool launch_fixed_nuts(const HmcArgs& a, int grid, size_t lds, hipStream_
 }
 
 // Team kernels: the default plans of the odd specialised sides, in the forms
-// whose lane columns split (team_waves).
-constexpr bool team_plan(int N, int P, int H) {
+// whose lane columns split (team_waves).  Under NUTS, where every point also
+// carries its bookkeeping, from 53 px on (16 transitions of 32 galaxies, C = 4:
+// 25 px 0.60 ms by teams and by one wave, 41 px 0.79 and 0.78, 53 px 0.91 and
+// 1.05, 73 px 0.75 and 0.89, 101 px 0.94 and 1.22).
+constexpr bool team_plan(int N, int P, int H, bool nuts) {
   return (N & 1) && P == make_slot_plan(N).P && team_waves(P * H) > 1 &&
-         (H == 1 || paired_chains_plan(N, P)) && (H < 4 || quad_chains_plan(N, P));
+         (H == 1 || paired_chains_plan(N, P)) && (H < 4 || quad_chains_plan(N, P)) &&
+         (!nuts || (N >= 53 && H <= 2));
 }
 
 // A team holds its chains' place on a compute unit with T waves instead of
@@ -1650,18 +1663,25 @@ constexpr bool team_plan(int N, int P, int H) {
 // 1.17 (2.44), 512 1.32 (2.50), 768 2.28 (2.24); at C = 1: 53 px 0.63 (1.02), 0.68
 // (1.03), 0.75 (1.08), 768 1.44 (0.85); 101 px 1 galaxy 0.98 (2.09), 256 1.03
 // (2.12), 512 1.33 (2.30).
-constexpr int team_groups(int N, int P, int H) {
-  const int waves = 4 * kHmcWavesPerEu / team_waves(P * H), lds = (int)(160 * 1024 / team_lds_bytes(N, P, H));
+constexpr int team_groups(int N, int P, int H, bool nuts) {
+  const int waves = 4 * kHmcWavesPerEu / team_waves(P * H);
+  const int lds = (int)(160 * 1024 / team_lds_bytes(N, P, H, nuts));
   return 256 * (waves < lds ? waves : lds);
 }
 
-template <int PROF, int NN, int PP, int H>
+// Waves of all the launches side by side: mixed batches of five sides, C = 4, 16
+// iterations: 400 galaxies (2,000 waves) 1.49 ms by teams and 2.48 by one wave,
+// 600 (3,000) 2.12 and 2.50; under NUTS, whose chains end one by one, 400 (1,600)
+// 1.76 and 1.87, 600 (with every side in teams, 3,400) 2.46 and 1.91.
+constexpr int team_side_waves(bool nuts) { return nuts ? 2048 : 3072; }
+
+template <int PROF, int NN, int PP, int H, bool NUTS>
 static bool launch_team_h(const HmcArgs& a, hipStream_t s) {
-  if constexpr (team_plan(NN, PP, H)) {
-    constexpr size_t lds = team_lds_bytes(NN, PP, H);
-    static_assert(team_groups(NN, PP, H) > 0, "team: beyond a compute unit's LDS");
-    if ((int64_t)std::max(a.n_gal, a.n_side) * (a.C / H) > team_groups(NN, PP, H)) return false;
-    auto k = hmc_team_kernel<PROF, PP, NN, H>;
+  if constexpr (team_plan(NN, PP, H, NUTS)) {
+    constexpr size_t lds = team_lds_bytes(NN, PP, H, NUTS);
+    static_assert(team_groups(NN, PP, H, NUTS) > 0, "team: beyond a compute unit's LDS");
+    if ((int64_t)a.n_gal * (a.C / H) > team_groups(NN, PP, H, NUTS)) return false;
+    auto k = hmc_team_kernel<PROF, PP, NN, H, NUTS>;
     (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(k, dim3(a.n_gal * (a.C / H)), dim3(kWave * team_waves(PP * H)), lds, s, a);
     return true;
@@ -1669,17 +1689,27 @@ static bool launch_team_h(const HmcArgs& a, hipStream_t s) {
   return false;
 }
 
+template <int PROF, int NN, int PP>
+static bool launch_team_p(const HmcArgs& a, int H, hipStream_t s) {
+  if (H == 4) return launch_team_h<PROF, NN, PP, 4, false>(a, s);
+  if (H == 2)
+    return a.nuts ? launch_team_h<PROF, NN, PP, 2, true>(a, s) : launch_team_h<PROF, NN, PP, 2, false>(a, s);
+  return a.nuts ? launch_team_h<PROF, NN, PP, 1, true>(a, s) : launch_team_h<PROF, NN, PP, 1, false>(a, s);
+}
+
 template <int PROF>
 static bool launch_team(const HmcArgs& a, int H, hipStream_t s) {
-#define BSI_CASE(NN, PP)                                                   \
-  if (a.N == NN && a.P == PP) {                                            \
-    if (H == 4) return launch_team_h<PROF, NN, PP, 4>(a, s);               \
-    if (H == 2) return launch_team_h<PROF, NN, PP, 2>(a, s);               \
-    return launch_team_h<PROF, NN, PP, 1>(a, s);                           \
-  }
+#define BSI_CASE(NN, PP) \
+  if (a.N == NN && a.P == PP) return launch_team_p<PROF, NN, PP>(a, H, s);
   BSI_FIXED_PLANS(BSI_CASE)
 #undef BSI_CASE
   return false;
+}
+
+int64_t hmc_team_waves(const HmcArgs& a) {
+  const int H = launch_chains_per_wave(a, false);
+  const bool team = !a.mx && a.wpc == 1 && a.prof != kProfGauss && team_plan(a.N, a.P, H, a.nuts);
+  return (int64_t)a.n_gal * (a.C / H) * (team ? team_waves(a.P * H) : a.wpc);
 }
 
 template <int PROF, bool INIT>
@@ -1744,7 +1774,8 @@ static hipError_t launch_impl(const HmcArgs& a, int grid, hipStream_t s) {
   // and launch_fixed_mx launch them
   const int H = launch_chains_per_wave(a, INIT);
   // teams (single steps stay with the plain kernels: staging would dominate)
-  if (!INIT && !a.nuts && !a.mx && a.wpc == 1 && a.n_steps > 1 && a.prof != kProfGauss &&
+  if (!INIT && !a.mx && a.wpc == 1 && a.n_steps > 1 && a.prof != kProfGauss &&
+      a.side_waves <= team_side_waves(a.nuts) &&
       (a.prof == kProfExp ? launch_team<kProfExp>(a, H, s) : launch_team<kProfSpergel>(a, H, s)))
     return hipGetLastError();
   const size_t lds = a.mx ? hmc_lds_bytes(a.N, a.C, a.P, 1, H, a.n_exp, true, a.nuts)

@@ -752,24 +752,33 @@ struct TeamLds {
   float* red;      // lane sums [64][8]
   float* own;      // this wave's reduction scratch (32 floats)
   double* chi2;    // per chain of the group
+  float4* res;     // RES: residuals of each pair [nsr PI][64]
+  float* c2;       // RES: |R|^2 by column block and super-row
 };
 
 // Columns per block in the order of the plain loops: kspace_sums_blocked with
 // four chains per wave, else all of them.
 constexpr int team_block(int PI, int H) { return H == 4 && PI > 6 ? 6 : PI; }
 
-// LDS of the above, in floats (all pieces 16-byte multiples).
-__host__ __device__ constexpr int team_floats(int nsr, int PI, int H) {
+// LDS of the above, in floats (all pieces 16-byte multiples).  RES: where every
+// evaluation needs |R|^2 (NUTS), the residuals go through LDS like the other
+// terms; where one in a trajectory does, the waves of a block take turns
+// (kspace_sums_team) and the LDS stays free for a second team (101 px: 79 KiB,
+// 127 with RES).
+__host__ __device__ constexpr int team_floats(int nsr, int PI, int H, bool res) {
   const int c2 = nsr * (PI / team_block(PI, H));
-  return 64 * (2 * nsr * PI + (c2 > 3 * PI ? c2 : 3 * PI)) + 512 + 32 * team_waves(PI) + 8;
+  return 64 * (2 * nsr * PI + (!res && c2 > 3 * PI ? c2 : 3 * PI)) + 512 + 32 * team_waves(PI) + 8 +
+         (res ? 64 * (4 * nsr * PI + c2) : 0);
 }
 
-template <int PI, int H>
+template <int PI, int H, bool RES>
 __device__ __forceinline__ TeamLds carve_team(float* at, int nsr, int part) {
   TeamLds l;
-  l.term = at;
+  l.res = reinterpret_cast<float4*>(at);
+  l.c2 = at + 256 * nsr * PI;
+  l.term = at + (RES ? 256 * nsr * PI + 64 * nsr * (PI / team_block(PI, H)) : 0);
   l.col = l.term + 128 * nsr * PI;
-  l.red = at + team_floats(nsr, PI, H) - (512 + 32 * team_waves(PI) + 8);
+  l.red = at + team_floats(nsr, PI, H, RES) - (512 + 32 * team_waves(PI) + 8);
   l.own = l.red + 512 + 32 * part;
   l.chi2 = reinterpret_cast<double*>(l.red + 512 + 32 * team_waves(PI));
   return l;
@@ -778,8 +787,9 @@ __device__ __forceinline__ TeamLds carve_team(float* at, int nsr, int part) {
 // What a lane of a team keeps in registers over a whole trajectory: its wave's
 // columns, the row factors of the sum the wave chains (part 0: ky^2, else ky)
 // and the lane's entry of its chain's tables (fill_team).
-template <int NFIX, int P, int H>
+template <int NFIX, int P, int H, bool RES_>
 struct TeamCols {
+  static constexpr bool RES = RES_;
   static constexpr int PI = P * H, T = team_waves(PI), NC = PI / T, K = make_slot_plan_p(NFIX, P).nsr;
   float kx[NC], kx2[NC];
   int xi[NC], yo[NC];
@@ -788,10 +798,10 @@ struct TeamCols {
   float fk, fa, fky;     // u or v, a(u) or a(v), k_v
 };
 
-template <int NFIX, int P, int H>
-__device__ __forceinline__ TeamCols<NFIX, P, H> team_cols(const float4* cols, const float* atab, const Geom& g,
-                                                          int part) {
-  using TC = TeamCols<NFIX, P, H>;
+template <int NFIX, int P, int H, bool RES>
+__device__ __forceinline__ TeamCols<NFIX, P, H, RES> team_cols(const float4* cols, const float* atab,
+                                                               const Geom& g, int part) {
+  using TC = TeamCols<NFIX, P, H, RES>;
   constexpr int LS = kWave / H, R = make_slot_plan_p(NFIX, P).R;
   TC c;
   const int lane = chain_lane<H>();
@@ -827,9 +837,9 @@ __device__ __forceinline__ TeamCols<NFIX, P, H> team_cols(const float4* cols, co
 
 // The tables of fill_tables (odd N), each entry by one lane of the team; the
 // zero entries (X[ntab], rows past hc) are written once by fill_team_zeros.
-template <int NFIX, int P, int H>
-__device__ __forceinline__ void fill_team(const TeamCols<NFIX, P, H>& c, const Geom& g, float2* X, float4* Ym,
-                                          float F, float dx, float dy) {
+template <class Cols>
+__device__ __forceinline__ void fill_team(const Cols& c, const Geom& g, float2* X, float4* Ym, float F, float dx,
+                                          float dy) {
   const float r = (c.fx >= 0 ? dx : dy) * rcp_nr((float)g.N);
   const float2 w = cis_neg_rev(c.fk * r);
   if (c.fx >= 0) {
@@ -848,12 +858,20 @@ __device__ __forceinline__ void fill_team_zeros(const Geom& g, const SlotPlan& s
   for (int v = g.hc + 1 + lane; v < sp.ymax; v += kWave / H) Ym[v] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-template <int PROF, int P, bool CHI2, int NFIX, int H>
-__device__ __forceinline__ KSums kspace_sums_team(const TeamCols<NFIX, P, H>& tc, const float4* cols,
+template <int H>
+__device__ __forceinline__ double chain_total(double x) {
+  if constexpr (H == 1)
+    return wave_total(x);
+  else
+    return group_total<H>(x);
+}
+
+template <int PROF, int P, bool CHI2, int NFIX, int H, bool RES>
+__device__ __forceinline__ KSums kspace_sums_team(const TeamCols<NFIX, P, H, RES>& tc, const float4* cols,
                                                   const float2* __restrict__ dh, const float2* X,
                                                   const float4* Ym, const Shape& sh, const TeamLds& l,
                                                   int part) {
-  using TC = TeamCols<NFIX, P, H>;
+  using TC = TeamCols<NFIX, P, H, RES>;
   constexpr SlotPlan spc = make_slot_plan_p(NFIX, P);
   constexpr int LS = kWave / H, PI = TC::PI, T = TC::T, NC = TC::NC, K = TC::K;
   // the order of the plain loops: by block of CB columns, within it by super-row
@@ -879,7 +897,8 @@ __device__ __forceinline__ KSums kspace_sums_team(const TeamCols<NFIX, P, H>& tc
     }
     const float4* dp = reinterpret_cast<const float4*>(dh) + lane + LS * c0;
     float* tp = l.term + 64 * c0 + wl;
-    if constexpr (!CHI2) {
+    if constexpr (!CHI2 || RES) {
+      float4* rp = l.res + 64 * c0 + wl;
       float4 Dn = dp[0];
       float4 yn = yq[0][0];
 #pragma unroll
@@ -896,6 +915,7 @@ __device__ __forceinline__ KSums kspace_sums_team(const TeamCols<NFIX, P, H>& tc
             pair_terms<PROF, false>(sh, D, y, xr[j], xi[j], TA[j], Tc[j], swq[j], wky[j], sdc[j]);
         tp[64 * (k * PI + j)] = t.ws;
         tp[64 * (K * PI + k * PI + j)] = t.gz;
+        if (CHI2) rp[64 * (k * PI + j)] = make_float4(t.Rpr, t.Rpi, t.Rmr, t.Rmi);
       }
     } else {
       // |R|^2 of a super-row runs over a block's columns: the waves that hold
@@ -994,11 +1014,23 @@ __device__ __forceinline__ KSums kspace_sums_team(const TeamCols<NFIX, P, H>& tc
     l.red[8 * wl + 3] = sxy;
     l.red[8 * wl + 4] = sdx;
   }
-  if (CHI2 && part == T - 1) {
-    if constexpr (H == 1)
-      chi2 = wave_total(chi2);
-    else
-      chi2 = group_total<H>(chi2);
+  if constexpr (CHI2 && RES) {
+    // |R|^2 of block q / K and super-row q % K, a row to a wave in turn
+#pragma unroll 1
+    for (int q = part; q < K * (PI / CB); q += T) {
+      const int k = q % K, i0 = q / K * CB;
+      float4 r[CB];
+#pragma unroll
+      for (int i = 0; i < CB; ++i) r[i] = l.res[64 * (k * PI + i0 + i) + wl];
+      __builtin_amdgcn_sched_barrier(0);
+      float c2 = 0.f;
+#pragma unroll
+      for (int i = 0; i < CB; ++i) c2 = pair_chi2(r[i].x, r[i].y, r[i].z, r[i].w, c2);
+      l.c2[64 * q + wl] = c2;
+    }
+  }
+  if (CHI2 && !RES && part == T - 1) {
+    chi2 = chain_total<H>(chi2);
     if (lane == 0) l.chi2[wl / LS] = chi2;
   }
   __syncthreads();
@@ -1008,14 +1040,20 @@ __device__ __forceinline__ KSums kspace_sums_team(const TeamCols<NFIX, P, H>& tc
     wave_gather7(v, l.red);
   else
     group_gather7<H>(v, l.red, l.own);
-  s.chi2 = CHI2 ? l.chi2[wl / LS] : 0.0;
+  if constexpr (CHI2 && RES) {
+#pragma unroll
+    for (int q = 0; q < K * (PI / CB); ++q) chi2 += (double)l.c2[64 * q + wl];
+    s.chi2 = chain_total<H>(chi2);
+  } else {
+    s.chi2 = CHI2 ? l.chi2[wl / LS] : 0.0;
+  }
   s.sF = v[0];
   s.sxx = v[1];
   s.syy = v[2];
   s.sxy = v[3];
   s.sdx = v[4];
   s.sdy = v[5];
-  s.sq = sh.ca * s.sxx + sh.cb * s.syy + sh.cc * s.sxy;
+  s.sq = fmaf(sh.cc, s.sxy, fmaf(sh.ca, s.sxx, sh.cb * s.syy));
   s.sF = flux_sum<PROF>(s.sF, s.sq, sh);
   return s;
 }
@@ -1023,7 +1061,10 @@ __device__ __forceinline__ KSums kspace_sums_team(const TeamCols<NFIX, P, H>& tc
 // Turn the sums into log L and d log L / d(F, s, e1, e2, dx, dy).
 // norm = 1 / (N^2 sigma^2); s_arcsec is the half-light radius.  The X table
 // carried the flux, so sF = sum Re(conj R T) and dT/dF = T / F.
-template <int PROF>
+// FUSED: the sums of two products rounded as the compiler fuses them in the
+// kernels of one wave per chain group, spelled out; which product of a sum it
+// fuses is its own choice in each kernel, and a team's draws are to be theirs.
+template <int PROF, bool FUSED = false>
 __device__ __forceinline__ KResult kspace_finish(const KSums& S, const Shape& sh, float F,
                                                  float s_arcsec, float e1, float e2, float norm) {
   KResult r;
@@ -1032,9 +1073,15 @@ __device__ __forceinline__ KResult kspace_finish(const KSums& S, const Shape& sh
   const float n2 = 2.0f * norm;                  // the halved sums doubled
   r.dF = n2 * S.sF * rcp_nr(F);
   r.ds = n2 * (2.0f * c * rcp_nr(s_arcsec)) * S.sq;
-  r.de1 = n2 * c * sh.inv1mE *
-          ((2.0f * e1 + 2.0f) * S.sxx + (2.0f * e1 - 2.0f) * S.syy + 2.0f * e1 * S.sq);
-  r.de2 = n2 * c * sh.inv1mE * (2.0f * e2 * (S.sxx + S.syy) + 4.0f * S.sxy + 2.0f * e2 * S.sq);
+  if constexpr (FUSED) {
+    r.de1 = n2 * c * sh.inv1mE *
+            fmaf(2.0f * e1, S.sq, fmaf(2.0f * e1 + 2.0f, S.sxx, (2.0f * e1 - 2.0f) * S.syy));
+    r.de2 = n2 * c * sh.inv1mE * fmaf(2.0f * e2, S.sq, fmaf(2.0f * e2, S.sxx + S.syy, 4.0f * S.sxy));
+  } else {
+    r.de1 = n2 * c * sh.inv1mE *
+            ((2.0f * e1 + 2.0f) * S.sxx + (2.0f * e1 - 2.0f) * S.syy + 2.0f * e1 * S.sq);
+    r.de2 = n2 * c * sh.inv1mE * (2.0f * e2 * (S.sxx + S.syy) + 4.0f * S.sxy + 2.0f * e2 * S.sq);
+  }
   r.ddx = n2 * S.sdx;
   r.ddy = n2 * S.sdy;
   return r;

@@ -496,7 +496,14 @@ int bsi_slots_advance(bsi_slots sv, int32_t n_iter) {
     }
   }
   HmcArgs base = base_args(sv);
-  for (int i : active) base.n_side += (int)sv->cls[i].resident.size();
+  for (int i : active) {
+    HmcArgs a = base;
+    a.N = sv->cls[i].N;
+    a.P = sv->cls[i].P;
+    a.wpc = sv->cls[i].W;
+    a.n_gal = (int)sv->cls[i].resident.size();
+    base.side_waves += hmc_team_waves(a);
+  }
   e = fork_join(h, sv->s, (int)active.size(), [&](int j, hipStream_t st) -> hipError_t {
     const int i = active[j];
     const SizeClass& k = sv->cls[i];
@@ -532,7 +539,7 @@ int bsi_slots_advance(bsi_slots sv, int32_t n_iter) {
     // a launch's duration follows one request's chain (the requests of a
     // size run side by side): its bins per wave, times its iterations
     const SizeClass& k = sv->cls[active[j]];
-    return (double)k.N * k.N / k.W * iters[active[j]];
+    return chain_cost(k.N) * iters[active[j]];
   });
   if (e != hipSuccess) return hip_fail(h, e, "advance launch");
   if (sv->ess) {

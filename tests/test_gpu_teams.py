@@ -18,12 +18,13 @@ def bsi(device):
     return api
 
 
-# (side, chains, profile, warmup, draws, leapfrog steps, jitter)
-CASES = [(25, 1, "exp", 3, 4, 5, 0.1), (25, 2, "exp", 3, 4, 5, 0.1), (25, 4, "exp", 3, 4, 5, 0.1),
-         (41, 2, "exp", 3, 4, 5, 0.0), (41, 4, "exp", 3, 4, 5, 0.1), (53, 1, "exp", 3, 4, 1, 0.1),
-         (53, 2, "exp", 3, 4, 5, 0.1), (53, 4, "exp", 10, 20, 20, 0.1), (73, 1, "exp", 3, 4, 5, 0.1),
-         (73, 3, "exp", 3, 4, 5, 0.1), (101, 1, "exp", 3, 4, 5, 0.1), (101, 4, "exp", 3, 4, 5, 0.1),
-         (53, 4, "spergel", 3, 4, 5, 0.1), (101, 1, "spergel", 3, 4, 5, 0.1)]
+# (side, chains, profile, warmup, draws, leapfrog steps or "nuts", jitter): every
+# team kernel, one step a trajectory, several launches, an odd number of chains
+FORMS = [(25, 1), (25, 2), (25, 4), (41, 2), (41, 4), (53, 1), (53, 2), (53, 4), (73, 1), (101, 1)]
+CASES = [(N, C, p, 5, 9, 7, 0.1) for N, C in FORMS for p in ("exp", "spergel")]
+CASES += [(N, C, p, 5, 9, "nuts", 0.0) for N, C in FORMS if N != 41 or C != 2 for p in ("exp", "spergel")]
+CASES += [(53, 1, "exp", 3, 4, 1, 0.1), (53, 4, "exp", 10, 20, 20, 0.1), (73, 3, "exp", 3, 4, 5, 0.0),
+          (101, 4, "exp", 3, 4, 5, 0.1), (73, 4, "exp", 3, 40, "nuts", 0.0)]
 
 
 @pytest.mark.parametrize("N,C,profile,warmup,draws,L,jitter", CASES)
@@ -37,8 +38,9 @@ def test_team_draws_are_one_waves(bsi, N, C, profile, warmup, draws, L, jitter):
         rep = lambda x: np.concatenate([x] * (n // 2)).astype(np.float32)
         b = bsi.Batch(n=np.full(n, N), psf_fwhm=torch.tensor(rep(t.psf_fwhm)).cuda(),
                       sigma=torch.tensor(rep(t.sigma)).cuda(), pixel_scale=gen.PIXEL_SCALE, profile=prof)
-        cfg = bsi.HmcConfig(n_chains=C, n_leapfrog=L, n_warmup=warmup, n_samples=draws, adapt=True,
-                            step_size=0.003, jitter=jitter, seed=5)
+        how = dict(sampler=bsi.N.SAMPLER_NUTS) if L == "nuts" else dict(n_leapfrog=L, jitter=jitter)
+        cfg = bsi.HmcConfig(n_chains=C, n_warmup=warmup, n_samples=draws, adapt=True, step_size=0.003, seed=5,
+                            **how)
         ref = torch.tensor(rep(np.stack([t.dx, t.dy], 1))).cuda()
         out = bsi.hmc_sample(b, torch.tensor(rep(data)).cuda(), ref, torch.tensor(rep(init)).cuda(), cfg)
         return [None if o is None else o[:2].cpu().numpy() for o in out]
