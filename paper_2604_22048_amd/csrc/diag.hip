@@ -266,7 +266,12 @@ hipError_t launch_ess(int n_gal, int C, int S, int P, const float* samples, floa
   // of six parameters)
   int q = std::min(P, kMaxPar), parts = 1;
   while (q > 1 && sizeof(float) * (size_t)ess_buf(S, q) > kEssLds) --q;
-  if ((int64_t)n_gal * P <= kFewSeries && C > 1) {
+  // few series: a workgroup each; of one chain only up to about 2 M draws in
+  // all, beyond which the strided reads cost more (C = 1, six parameters, a
+  // parameter / a galaxy per workgroup: 100 x 200 draws 10.1 / 10.8 us, 100 x 2,000
+  // 18.2 / 24.1, 500 x 500 15.1 / 15.7, 200 x 2,000 26.0 / 24.5)
+  const int64_t series = (int64_t)n_gal * P;
+  if (series <= kFewSeries && (C > 1 || series * S <= 2'000'000)) {
     q = 1;
     parts = std::min(C, kMaxParts);
     while (parts > 1 && parts * sizeof(float) * (size_t)ess_buf(S, 1) > kEssLds) --parts;

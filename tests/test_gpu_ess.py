@@ -19,7 +19,8 @@ def bsi(device):
 SHAPES = [(3, 1, 4, 1, 0), (2, 16, 15, 6, 0), (2, 2, 16, 5, 1), (3, 4, 17, 9, 2), (1, 4, 1024, 6, 3),
           (2, 2, 1041, 7, 40), (1, 3, 2500, 6, 200), (1, 1, 18944, 2, 30),
           (1, 11, 321, 3, 0), (3100, 2, 33, 1, 1), (1600, 1, 320, 2, 0), (800, 3, 577, 4, 2), (400, 2, 90, 8, 30),
-          (400, 2, 600, 9, 0), (700, 2, 1089, 5, 4)]
+          (400, 2, 600, 9, 0), (700, 2, 1089, 5, 4),
+          (100, 1, 200, 6, 3), (30, 1, 2000, 7, 20)]
 
 
 @pytest.mark.parametrize("G,C,S,P,memory", SHAPES)
