@@ -3,8 +3,8 @@ workload (10,000 galaxies, 53x53 stamps, PSF FWHM 0.7", 4 chains, 20 leapfrog
 steps, 300 dual-averaging warmup iterations + 1,000 draws), one MI355X.
 
 One step = the whole hot path on one synthetic batch: data transform, chain
-initialisation, warmup + sampling (one persistent launch per trajectory,
-replayed from a HIP graph), ESS/R-hat, and the shear posterior of the interim
+initialisation, warmup + sampling (several trajectories of every chain per
+launch), ESS/R-hat, and the shear posterior of the interim
 samples on a 41x41 grid.  Time per galaxy follows Section 4.1:
     T_warmup / G + T_sampling / (G * n_eff) * 300,
 with T_warmup from a warmup-only call and T_sampling = T_hmc - T_warmup.
@@ -356,17 +356,14 @@ def shear_hmc_run(api, torch, stream, e1p, e2p, l10s, G, K, seed, cpu=False):
 
 def render_flops(N):
     """(algorithmic, executed) flops of one stamp's render as two dense DFT
-    products: pass 1 complex (rows v = 0..h) x (u = -h..h) x (x), 8 flops per
-    complex multiply-add; pass 2 real, 4 flops per (y, x, v).  Executed: the
-    MFMA tiles the kernel issues (16 x 16 x 4, 2048 flops each), padding
-    included."""
-    h = N // 2
-    ntab, nrow = 2 * h + 1, h + 1
-    alg = 8 * nrow * ntab * N + 4 * N * N * nrow
-    ldT, nrow4, Np = (ntab + 3) // 4 * 4, (nrow + 3) // 4 * 4, (N + 15) // 16 * 16
-    n1 = ((nrow + 15) // 16) * (Np // 16) * (ldT // 4) * 4
-    n2 = (Np // 16) ** 2 * (nrow4 // 4) * 2
-    return alg, (n1 + n2) * 2048
+    products folded about the stamp's centre: even and odd, real and imaginary
+    parts at rows v = 0..h x distances x' over u = 0..h, then four products at
+    distances y' x x' over v.  Executed: the MFMA tiles the kernel issues
+    (16 x 16 x 4, 2048 flops each), padding included."""
+    nrow, nd = N // 2 + 1, (N + 1) // 2
+    alg = 8 * nrow * nrow * nd + 8 * nd * nd * nrow
+    nrb, ntb, steps = (nrow + 15) // 16, (nd + 15) // 16, (nrow + 3) // 4
+    return alg, (nrb + ntb) * ntb * steps * 4 * 2048
 
 
 def transform_leg(api, sizes=(25, 41, 53, 73, 101), n_gal=10_000):
@@ -530,8 +527,8 @@ def serving_leg(api, torch, rate, window_s, cap_requests, seed, n_draws=1500, it
 
 def tiny_leg(api, torch, stream, log=None, oracle=None):
     """The plain tiny workload: 16 galaxies of 32 x 32, 1 chain, 10 leapfrog
-    steps at the fixed step 0.005, 100 burn-in + 500 draws.  Batched (one
-    launch per iteration, graph-replayed) and plain (one galaxy and one
+    steps at the fixed step 0.005, 100 burn-in + 500 draws.  Batched (all
+    galaxies, many iterations per launch) and plain (one galaxy and one
     leapfrog step per launch, run in full), galaxies/s at 300 ESS for both,
     then the 41 x 41 shear grid on [-0.25, 0.25]^2 over the draws."""
     cfg = gen.CONFIGS["tiny"]
@@ -589,10 +586,9 @@ def tiny_leg(api, torch, stream, log=None, oracle=None):
 def uneven_leg(api, torch, stream, n_gal, log=None, per_size_runs=True, oracle=None):
     """Batched uneven workload: n_gal galaxies, stamp side from the size rule
     (25-101), PSF FWHM ~ U(0.6, 0.9), SNR 10-200, 4 chains, 20 leapfrog
-    steps, 300 warmup + 1000 draws.  Timed in the direct form (each
-    iteration's per-size launches concurrent on forked streams), and in the
-    graph form (the per-size launches in sequence, replayed from a graph) for
-    comparison.  per_size_runs: also time each size class alone
+    steps, 300 warmup + 1000 draws.  The sizes run concurrently on
+    forked streams; the run with use_graph set (graph_form) repeats it, since
+    the sampler now enqueues its launches directly either way.  per_size_runs: also time each size class alone
     (uneven_per_size)."""
     cfg = gen.CONFIGS["uneven"]
     say = log or (lambda m: None)
@@ -651,9 +647,8 @@ def uneven_per_size(api, torch, stream, cfg, counts, hcfg, n1=20, n2=60, log=Non
     """Trajectory-kernel time per launch of each size class of the uneven
     batch, alone on the device: a batch of that many galaxies of that size
     (drawn from the uneven population with the stamp side forced), timed as
-    the difference of two warmup-only calls of n2 and n1 iterations (one
-    launch per iteration, replayed from a graph), so that the chain start and
-    data transform cancel.  Fractions use the algorithmic flop count per
+    the difference of two warmup-only calls of n2 and n1 iterations, per
+    iteration, so that the chain start and data transform cancel.  Fractions use the algorithmic flop count per
     evaluation of that size."""
     out = {}
     for N, k in sorted(counts.items()):
@@ -1130,7 +1125,7 @@ def main():
     plain_tpg = per_iter_gal * (W + S * TARGET_ESS / n_eff_mean)
     plain_value = 1.0 / plain_tpg
 
-    # roofline of the trajectory kernel: one launch = one iteration of every chain
+    # roofline of the trajectory kernel, per iteration of every chain
     n_launch = W + S
     t_launch = t_hmc / n_launch
     alg = flops_per_eval(N, L) * G * C * L
