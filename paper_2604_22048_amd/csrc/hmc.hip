@@ -1708,7 +1708,7 @@ static bool launch_team(const HmcArgs& a, int H, hipStream_t s) {
 
 int64_t hmc_team_waves(const HmcArgs& a) {
   const int H = launch_chains_per_wave(a, false);
-  const bool team = !a.mx && a.wpc == 1 && a.prof != kProfGauss && team_plan(a.N, a.P, H, a.nuts);
+  const bool team = !a.mx && a.wpc == 1 && a.C <= 4 && a.prof != kProfGauss && team_plan(a.N, a.P, H, a.nuts);
   return (int64_t)a.n_gal * (a.C / H) * (team ? team_waves(a.P * H) : a.wpc);
 }
 
@@ -1773,8 +1773,10 @@ static hipError_t launch_impl(const HmcArgs& a, int grid, hipStream_t s) {
   // several chains per wave exactly where launch_fixed_w, launch_fixed_nuts
   // and launch_fixed_mx launch them
   const int H = launch_chains_per_wave(a, INIT);
-  // teams (single steps stay with the plain kernels: staging would dominate)
-  if (!INIT && !a.mx && a.wpc == 1 && a.n_steps > 1 && a.prof != kProfGauss &&
+  // teams, in place of the specialised one-wave kernels (C <= 4; more chains run
+  // on the general ones, which may round otherwise); single steps stay with one
+  // wave: staging would dominate
+  if (!INIT && !a.mx && a.wpc == 1 && a.C <= 4 && a.n_steps > 1 && a.prof != kProfGauss &&
       a.side_waves <= team_side_waves(a.nuts) &&
       (a.prof == kProfExp ? launch_team<kProfExp>(a, H, s) : launch_team<kProfSpergel>(a, H, s)))
     return hipGetLastError();

@@ -24,7 +24,8 @@ FORMS = [(25, 1), (25, 2), (25, 4), (41, 2), (41, 4), (53, 1), (53, 2), (53, 4),
 CASES = [(N, C, p, 5, 9, 7, 0.1) for N, C in FORMS for p in ("exp", "spergel")]
 CASES += [(N, C, p, 5, 9, "nuts", 0.0) for N, C in FORMS if N != 41 or C != 2 for p in ("exp", "spergel")]
 CASES += [(53, 1, "exp", 3, 4, 1, 0.1), (53, 4, "exp", 10, 20, 20, 0.1), (73, 3, "exp", 3, 4, 5, 0.0),
-          (101, 4, "exp", 3, 4, 5, 0.1), (73, 4, "exp", 3, 40, "nuts", 0.0)]
+          (101, 4, "exp", 3, 4, 5, 0.1), (73, 4, "exp", 3, 40, "nuts", 0.0), (53, 8, "exp", 3, 4, 5, 0.1),
+          (73, 5, "exp", 3, 4, "nuts", 0.0)]
 
 
 @pytest.mark.parametrize("N,C,profile,warmup,draws,L,jitter", CASES)
