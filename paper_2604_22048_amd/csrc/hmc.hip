@@ -1331,11 +1331,11 @@ constexpr size_t team_lds_bytes(int N, int P, int H, bool nuts) {
 }
 
 // One workgroup of T waves per group of H chains (the chains that share a wave
-// in hmc_kernel): one exposure, odd stamp sides.  For launches with fewer chain groups than the chip has SIMDs: an evaluation
-// of four chains at 53 px takes one wave 5.3 us, most of it the wave's own
-// instruction issue; a team's 2.6 us are the longest wave's issue (12 pairs of 42
-// instructions at 4 cycles, 0.85 us), the serial part that every wave repeats and
-// the three barriers.
+// in hmc_kernel): one exposure, odd stamp sides.  For launches with fewer chain
+// groups than the chip has SIMDs: an evaluation of four chains at 53 px takes
+// one wave 5.3 us, most of it the wave's own instruction issue; a team's 2.5 us
+// are the longest wave's issue (12 pairs of 42 instructions at 4 cycles, 0.85
+// us), the serial part that every wave repeats and the three barriers.
 template <int PROF, int P, int NFIX, int H, bool NUTS>
 __global__ void __launch_bounds__(kWave * team_waves(P * H), kHmcWavesPerEu) hmc_team_kernel(HmcArgs a) {
   static_assert(!NUTS || H <= 2, "NUTS: one or two chains per wave");
