@@ -220,6 +220,19 @@ hipError_t for_classes(bsi_handle h, const Plan& p, hipStream_t s, bool cap, F&&
 // other streams' work gets onto the device.  The samples do not depend on it.
 constexpr int kLaunchEvals = 512;
 
+}  // namespace
+
+// A launch's iterations are at most iters_per_launch (which may be the largest
+// int) or kLaunchEvals evaluations' worth (a NUTS transition counted as 16),
+// and its steps fit an int.
+int bsi::hmc_launches(int T, int iters_per_launch, int L, bool nuts) {
+  int most = std::max(iters_per_launch, kLaunchEvals / (nuts ? 16 : std::min(L, kLaunchEvals)));
+  most = std::min(most, nuts ? T : std::min(T, INT32_MAX / L));
+  return T > 0 ? (int)(((int64_t)T + most - 1) / most) : 0;
+}
+
+namespace {
+
 // Every workspace buffer of a handle (an array: an initializer_list returned
 // from a function would refer to a temporary that dies with the return).
 std::array<DevBuf*, 14> all_buffers(bsi_handle h) {
@@ -602,10 +615,8 @@ int bsi_hmc_sample(bsi_handle h, const bsi_batch* batch, const float* data, cons
 
   const int T = a.t_stop;
   const bool plain = cfg->form == BSI_FORM_PLAIN;
-  // batched form: the iterations in as few launches of at most this many as
-  // possible (a NUTS transition counted as 16 evaluations)
-  const int most = std::max(cfg->iters_per_launch, kLaunchEvals / (nuts ? 16 : std::min(a.L, kLaunchEvals)));
-  const int n_launch = (T + most - 1) / most;
+  // batched form: the iterations in as few launches as possible
+  const int n_launch = hmc_launches(T, cfg->iters_per_launch, a.L, nuts);
   hipError_t e = for_classes(h, p, s, cap, [&](const ClassRange& c, hipStream_t st) -> hipError_t {
     hipError_t x = class_spectrum(h, p, c, data, nullptr, nullptr, st);
     if (x == hipSuccess && mx) x = class_weights(h, batch, p, c, st);
