@@ -406,8 +406,9 @@ int bsi_render_stamps(bsi_handle h, const bsi_batch* batch, const float* params,
   const bool cap = capturing(s);
   const Plan p = make_plan(h, batch, transform_of(h, batch->n[0]) == BSI_TRANSFORM_MFMA, false);
   const PlanBytes pb = plan_bytes(batch, p);
-  if (!p.packed && (rc = prepare(h, s, cap, {{&h->gidx, pb.gidx}, {&h->off, pb.off}, {&h->bin_off, pb.bin_off},
-                                             {&h->ggidx, pb.ggidx}}, pb.stage())))
+  // (a packed batch needs no workspace, but takes its place in the handle's order of calls)
+  if ((rc = prepare(h, s, cap, {{&h->gidx, pb.gidx}, {&h->off, pb.off}, {&h->bin_off, pb.bin_off},
+                                {&h->ggidx, pb.ggidx}}, pb.stage())))
     return rc;
   if ((rc = upload_plan(h, batch, p, s, cap))) return rc;
   const float rs = profile_rscale(batch->profile, batch->pixel_scale, batch->spergel_nu);
@@ -418,7 +419,7 @@ int bsi_render_stamps(bsi_handle h, const bsi_batch* batch, const float* params,
                   batch->profile, batch->spergel_nu, out, st, p.E);
   });
   if (e != hipSuccess) return hip_fail(h, e, "render launch");
-  return p.packed ? BSI_OK : finish(h, s, cap);
+  return finish(h, s, cap);
 }
 
 int bsi_loglik_grad(bsi_handle h, const bsi_batch* batch, const float* data, const float* params,
@@ -447,9 +448,7 @@ int bsi_loglik_grad(bsi_handle h, const bsi_batch* batch, const float* data, con
   const PlanBytes pb = plan_bytes(batch, p);
   bool spectra = false;
   for (const ClassRange& c : p.classes) spectra |= !fused(c.N, c.count);
-  const bool workspace = !p.packed || pixel;
-  if (workspace &&
-      (rc = prepare(h, s, cap,
+  if ((rc = prepare(h, s, cap,
                     {{&h->gidx, pb.gidx}, {&h->off, pb.off}, {&h->bin_off, pb.bin_off},
                      {&h->ggidx, pb.ggidx}, {&h->dh, spectra ? (size_t)p.total_bins * sizeof(float2) : 0},
                      {&h->sqw, spectra && mx ? (size_t)p.total_bins * sizeof(float) : 0},
@@ -496,7 +495,7 @@ int bsi_loglik_grad(bsi_handle h, const bsi_batch* batch, const float* data, con
     return x == hipSuccess ? launch_loglik(ac, batch->profile, pixel, mx, st) : x;
   });
   if (e != hipSuccess) return hip_fail(h, e, "loglik launch");
-  return workspace ? finish(h, s, cap) : BSI_OK;
+  return finish(h, s, cap);
 }
 
 int bsi_hmc_sample(bsi_handle h, const bsi_batch* batch, const float* data, const float* ref_xy,
