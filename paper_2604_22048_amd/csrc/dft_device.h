@@ -65,11 +65,25 @@ __host__ __device__ constexpr int dft_tab_off(int N) {
 // {k_u, sinc(u / N)} pairs, u = 0..h, of one side.
 constexpr int kSincLen = 65;
 
+// Units of work of the passes: pairs of row blocks by column blocks (A), row
+// blocks by table blocks (B).  A wave holds up to U of either in registers.
+__host__ __device__ constexpr int dft_units(int N) {
+  const DftDims d = dft_dims(N);
+  const int a = (d.nrb + 1) / 2 * d.ncb, b = d.nrb * d.nblk - (d.nblk > d.nrb ? d.nrb : 0);
+  return a > b ? a : b;
+}
+
+// Units a wave of at most 8 holds: one, two, or four (128 px).
+__host__ __device__ constexpr int dft_per_wave(int N) { return dft_units(N) <= 8 ? 1 : dft_units(N) <= 16 ? 2 : 4; }
+
+// Stamps whose table exceeds the LDS beside the rest: it is read from memory.
+__host__ __device__ constexpr bool dft_big(int N) { return dft_per_wave(N) > 2; }
+
 // K steps whose operands are on their way while others are multiplied (a step's
 // MFMAs take 64 to 256 cycles, LDS reads about 100, the tables from L2, for
 // stamps whose tables exceed LDS, several hundred).  The last ones read up to
-// kAhead steps past the operands' end, within the regions' padding, and are
-// not used.
+// kAhead steps past the operands' end, within the workgroup's LDS and the
+// tables' padding, and are not used.
 constexpr int kAhead = 4;
 
 // LDS of stamp_dft: one region that holds the stamp (float, zero rows up to a
@@ -82,20 +96,13 @@ struct DftLds {
 
 __host__ __device__ inline DftLds dft_lds(int N, const SlotPlan& sp) {
   const DftDims d = dft_dims(N);
-  // (reads past the stamp, up to kAhead steps, fall into what follows)
-  const size_t a = sizeof(float) * ((size_t)4 * d.steps * N + 64);
+  // steps read ahead past the stamp fall into what follows it, the table above
+  // all, or without one (dft_big) into the region itself
+  const size_t a = sizeof(float) * ((size_t)4 * (d.steps + (dft_big(N) ? kAhead : 0)) * N + 64);
   const size_t q = sizeof(float2) * ((size_t)d.nrow * d.ldQ + 4 * kAhead), b = sizeof(float2) * (size_t)sp.nbins;
   const size_t m = a > q ? a : q;
   return {((m > b ? m : b) + 15) & ~(size_t)15, sizeof(float2) * ((size_t)d.nblk * d.steps + kAhead) * 64,
           sizeof(int) * (size_t)d.nrb * 16};
-}
-
-// Units of work of the passes: pairs of row blocks by column blocks (A), row
-// blocks by table blocks (B).  A wave holds up to U of either in registers.
-__host__ __device__ constexpr int dft_units(int N) {
-  const DftDims d = dft_dims(N);
-  const int a = (d.nrb + 1) / 2 * d.ncb, b = d.nrb * d.nblk - (d.nblk > d.nrb ? d.nrb : 0);
-  return a > b ? a : b;
 }
 
 // Pair-slot of (0, v) for every row v (16 entries per row block).
@@ -383,12 +390,6 @@ __device__ __forceinline__ void stamp_dft(int N, const SlotPlan& sp, const float
     if (MX) sqw[t] = 0.f;
   }
 }
-
-// Units a wave of at most 8 holds: one, two, or four (128 px).
-constexpr int dft_per_wave(int N) { return dft_units(N) <= 8 ? 1 : dft_units(N) <= 16 ? 2 : 4; }
-
-// Stamps whose table exceeds the LDS beside the rest: it is read from memory.
-constexpr bool dft_big(int N) { return dft_per_wave(N) > 2; }
 
 // Waves per workgroup (one stamp at a time) of the transform: one unit each up
 // to 8 waves (10,000 stamps of 53 px 172 us so, 275 with two waves of two units
