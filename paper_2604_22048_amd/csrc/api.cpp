@@ -213,20 +213,20 @@ hipError_t for_classes(bsi_handle h, const Plan& p, hipStream_t s, bool cap, F&&
   return for_classes(h, p, s, cap, fn, [](const ClassRange& c) { return (double)c.N * c.N * c.gcount; });
 }
 
-// Leapfrog evaluations of a chain per launch, about: a launch costs 6 us plus
-// the galaxy's staging (its spectrum, the PSF table in float64, the chain
-// states), 10 % of a 20-step trajectory of a single 53-pixel galaxy, and an
-// evaluation 2 to 20 us, so that a workgroup still ends within about 10 ms and
-// other streams' work gets onto the device.  The samples do not depend on it.
+// Leapfrog evaluations of a chain per launch: a launch costs 6 us plus the
+// galaxy's staging (its spectrum, the PSF table in float64, the chain states),
+// 10 % of a 20-step trajectory of a single 53-pixel galaxy, and an evaluation 2
+// to 20 us, so that a workgroup still ends within about 10 ms and other
+// streams' work gets onto the device.  The samples do not depend on it.
 constexpr int kLaunchEvals = 512;
 
 }  // namespace
 
 // A launch's iterations are at most iters_per_launch (which may be the largest
-// int) or kLaunchEvals evaluations' worth (a NUTS transition counted as 16),
-// and its steps fit an int.
-int bsi::hmc_launches(int T, int iters_per_launch, int L, bool nuts) {
-  int most = std::max(iters_per_launch, kLaunchEvals / (nuts ? 16 : std::min(L, kLaunchEvals)));
+// int) or those that take kLaunchEvals evaluations at most, a NUTS transition
+// up to 2^max_depth; and its steps fit an int.
+int bsi::hmc_launches(int T, int iters_per_launch, int L, bool nuts, int max_depth) {
+  int most = std::max({iters_per_launch, 1, nuts ? kLaunchEvals >> max_depth : kLaunchEvals / L});
   most = std::min(most, nuts ? T : std::min(T, INT32_MAX / L));
   return T > 0 ? (int)(((int64_t)T + most - 1) / most) : 0;
 }
@@ -615,7 +615,7 @@ int bsi_hmc_sample(bsi_handle h, const bsi_batch* batch, const float* data, cons
   const int T = a.t_stop;
   const bool plain = cfg->form == BSI_FORM_PLAIN;
   // batched form: the iterations in as few launches as possible
-  const int n_launch = hmc_launches(T, cfg->iters_per_launch, a.L, nuts);
+  const int n_launch = hmc_launches(T, cfg->iters_per_launch, a.L, nuts, a.max_depth);
   hipError_t e = for_classes(h, p, s, cap, [&](const ClassRange& c, hipStream_t st) -> hipError_t {
     hipError_t x = class_spectrum(h, p, c, data, nullptr, nullptr, st);
     if (x == hipSuccess && mx) x = class_weights(h, batch, p, c, st);

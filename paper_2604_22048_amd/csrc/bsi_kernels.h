@@ -181,7 +181,7 @@ size_t hmc_lds_bytes(int N, int C, int P, int W, int H = 1, int E = 1, bool mx =
 // specialised kernel.
 int hmc_split_waves(int N, int C, int P, int prof, int max_w);
 // Advance launches (api.cpp) of a size's T iterations in the batched form.
-int hmc_launches(int T, int iters_per_launch, int L, bool nuts);
+int hmc_launches(int T, int iters_per_launch, int L, bool nuts, int max_depth);
 // Whether the advance kernel with exposures / noise weights (mx) runs on the
 // kernels specialised for stamp side N: one wave per chain, the exponential or
 // Spergel profile and P N's default plan with a specialised kernel.

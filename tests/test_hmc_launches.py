@@ -10,9 +10,9 @@ INT_MAX = 2**31 - 1
 @pytest.fixture(scope="module")
 def launches():
     from paper_2604_22048_amd import _native
-    f = _native.load()._ZN3bsi12hmc_launchesEiiib
-    f.restype, f.argtypes = C.c_int, [C.c_int, C.c_int, C.c_int, C.c_bool]
-    return f
+    f = _native.load()._ZN3bsi12hmc_launchesEiiibi
+    f.restype, f.argtypes = C.c_int, [C.c_int, C.c_int, C.c_int, C.c_bool, C.c_int]
+    return lambda T, ipl, L, nuts, depth=5: f(T, ipl, L, nuts, depth)
 
 
 @pytest.mark.parametrize("nuts", [False, True])
@@ -31,3 +31,13 @@ def test_short_launches_are_merged_and_long_ones_fit_an_int(launches):
     for T, L in ((1300, 20_000_000), (5000, 500_000)):
         n = launches(T, INT_MAX, L, False)
         assert -(-T // n) * L <= INT_MAX
+
+
+@pytest.mark.parametrize("depth", range(1, 11))
+def test_merged_nuts_launches_end_within_512_evaluations(launches, depth):
+    """However deep the trees, unless a launch is a single transition or asked for."""
+    T = 200
+    n = launches(T, 1, 20, True, depth)
+    most = -(-T // n)
+    assert most == 1 or most * 2**depth <= 512
+    assert n <= -(-T * 2**depth // 512) and launches(T, 50, 20, True, depth) <= 4
