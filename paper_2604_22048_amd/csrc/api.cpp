@@ -604,10 +604,14 @@ int bsi_hmc_sample(bsi_handle h, const bsi_batch* batch, const float* data, cons
   a.off = static_cast<const int64_t*>(h->off.p);
   a.nuts = nuts ? 1 : 0;
   a.max_depth = cfg->max_tree_depth;
+  auto waves = [&](const ClassRange& c) {      // per chain
+    return (mx || nuts) ? 1 : hmc_split_waves(c.N, C, c.P, batch->profile, cfg->waves_per_chain);
+  };
   for (const ClassRange& c : p.classes) {
     HmcArgs ac = a;
     ac.N = c.N;
     ac.P = c.P;
+    ac.wpc = waves(c);
     ac.n_gal = c.gcount;
     a.side_waves += hmc_team_waves(ac);
   }
@@ -635,7 +639,7 @@ int bsi_hmc_sample(bsi_handle h, const bsi_batch* batch, const float* data, cons
           x = launch_hmc_advance(ac, 1, st);
       return x;
     }
-    ac.wpc = (mx || nuts) ? 1 : hmc_split_waves(c.N, C, c.P, batch->profile, cfg->waves_per_chain);
+    ac.wpc = waves(c);
     for (int k = 0; x == hipSuccess && k < n_launch; ++k) {
       // evenly sized launches: iterations [k T / n, (k + 1) T / n)
       const int it = (int)((int64_t)(k + 1) * T / n_launch - (int64_t)k * T / n_launch);
@@ -643,7 +647,7 @@ int bsi_hmc_sample(bsi_handle h, const bsi_batch* batch, const float* data, cons
       x = launch_hmc_advance(ac, c.gcount, st);
     }
     return x;
-  }, [](const ClassRange& c) { return chain_cost(c.N) * std::max(1.0, c.gcount / 512.0); });
+  }, [&](const ClassRange& c) { return chain_cost(c.N, waves(c)) * std::max(1.0, c.gcount / 512.0); });
   if (e != hipSuccess) return hip_fail(h, e, "hmc launch");
   e = launch_hmc_finalize(static_cast<const ChainState*>(h->state.p), batch->n_gal, C, cfg->n_samples,
                           chain_stats, status, s);

@@ -537,9 +537,9 @@ int bsi_slots_advance(bsi_slots sv, int32_t n_iter) {
     return x;
   }, [&](int j) {
     // a launch's duration follows one request's chain (the requests of a
-    // size run side by side): its bins per wave, times its iterations
+    // size run side by side), times its iterations
     const SizeClass& k = sv->cls[active[j]];
-    return chain_cost(k.N) * iters[active[j]];
+    return chain_cost(k.N, k.W) * iters[active[j]];
   });
   if (e != hipSuccess) return hip_fail(h, e, "advance launch");
   if (sv->ess) {
