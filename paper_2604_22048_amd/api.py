@@ -125,9 +125,11 @@ def render_stamps(batch: Batch, params: torch.Tensor, lib: Library | None = None
     lib = lib or get(params.device.index or 0)
     params = params.contiguous().float()
     assert params.shape == (batch.n_gal, 6)
-    # every pixel is written where the stamps lie back to back; gaps are zero
+    # every pixel is written where the galaxies' stamps lie back to back; gaps,
+    # and stamps past the last galaxy's exposures, are zero
     end = batch.off + batch.n.astype(np.int64) ** 2
-    packed = batch.n_gal > 0 and batch.off[0] == 0 and np.array_equal(batch.off[1:], end[:-1])
+    packed = (0 < len(batch.n) == batch.n_gal * max(1, int(batch.n_exp)) and batch.off[0] == 0
+              and np.array_equal(batch.off[1:], end[:-1]))
     alloc = torch.empty if packed else torch.zeros
     out = alloc(batch.n_pixels, dtype=torch.float32, device=params.device)
     b = batch.c()
