@@ -121,23 +121,24 @@ __global__ void __launch_bounds__(q > 1 ? kWave * q : kWave * kMaxParts, q > 4 ?
   // chain c's mean, and its halves' means and squared deviations (draws [0, h)
   // and [S - h, S); the middle draw of an odd S is in neither)
   auto moments = [&](int c, const float* col) {
-    double sa = 0.0, st = 0.0;
+    double sa = 0.0, sb = 0.0;
 #pragma clang loop unroll(disable)
     for (int s = kRun * lane; s < S; s += kRun * kWave) {
-      const int na = h - s, nv = S - s;
+      const int na = h - s, nb = S - h - s, nv = S - s;
 #pragma unroll
       for (int j = 0; j < kRun; ++j) {
-        const float f = j < nv ? col[(s + j) * q] : 0.f;
-        st += (double)f;
+        const float f = col[(s + j) * q];
         sa += (double)(j < na ? f : 0.f);
+        sb += (double)((j >= nb) & (j < nv) ? f : 0.f);
         if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
       }
     }
-    st = wave_total(st);
+    sa = wave_total(sa);
+    sb = wave_total(sb);
+    const double st = (S & 1) ? sa + sb + (double)col[h * q] : sa + sb;
     if (lane == 0) mean_s[w][c] = st / S;
     if (rsplit) {
-      sa = wave_total(sa);
-      const double ma = sa / h, mb = (st - sa - ((S & 1) ? (double)col[h * q] : 0.0)) / h;
+      const double ma = sa / h, mb = sb / h;
 #pragma clang loop unroll(disable)
       for (int s = kRun * lane; s < S; s += kRun * kWave) {
         const int na = h - s, nb = S - h - s, nv = S - s;

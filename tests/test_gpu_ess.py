@@ -59,3 +59,17 @@ def test_ess_constant_chains(bsi):
     assert torch.all(e[0] == 200)
     # rho = 1 at every lag: tau = -1 + 2 (2 S / 2) = 199
     assert torch.allclose(e[1].cpu(), torch.full((2,), 200 / 199.0), rtol=2.0 ** -23)
+
+
+@pytest.mark.parametrize("G,C,S,P", [(2, 1, 5, 6), (3, 2, 7, 1), (2, 3, 333, 9), (700, 4, 601, 6)])
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), -float("inf"), 1e30])
+def test_split_rhat_leaves_the_middle_draw_out(bsi, G, C, S, P, value):
+    """An odd chain's middle draw is in neither half, whatever it holds."""
+    import torch
+    x = np.random.default_rng(S).normal(size=(G, C, S, P)).astype(np.float32)
+    y = x.copy()
+    y[0, 0, S // 2, 0] = y[-1, -1, S // 2, -1] = value
+    rs = bsi.ess(torch.tensor(x).cuda(), split=True)[2].cpu().numpy()
+    out = [a.cpu().numpy() for a in bsi.ess(torch.tensor(y).cuda(), split=True)]
+    assert np.array_equal(out[2], rs)
+    assert np.isfinite(out[0][-1, -1]) == (abs(value) < 1e31) or out[0][-1, -1] == C * S
