@@ -73,3 +73,29 @@ def test_split_rhat_leaves_the_middle_draw_out(bsi, G, C, S, P, value):
     out = [a.cpu().numpy() for a in bsi.ess(torch.tensor(y).cuda(), split=True)]
     assert np.array_equal(out[2], rs)
     assert np.isfinite(out[0][-1, -1]) == (abs(value) < 1e31) or out[0][-1, -1] == C * S
+
+
+# slowly mixing chains, whose scan goes on for many blocks of 16 lags: one to eight
+# waves a series, blocks side by side, galaxies that do not fill the XCDs' turns
+@pytest.mark.parametrize("G,C,S,P,memory", [(9, 2, 100, 5, 50), (100, 2, 100, 5, 80), (17, 4, 300, 20, 60),
+                                            (1, 1, 2000, 1, 400), (41, 8, 500, 3, 100), (1030, 4, 60, 2, 10),
+                                            (601, 3, 1000, 6, 30), (1, 16, 1184, 6, 50), (2051, 1, 257, 2, 40)])
+def test_ess_of_slowly_mixing_chains(bsi, G, C, S, P, memory):
+    test_ess_layout_edges(bsi, G, C, S, P, memory)
+
+
+@pytest.mark.parametrize("G,C,S,P", [(3, 2, 40, 3), (700, 4, 1000, 6)])
+def test_ess_outputs_alone(bsi, G, C, S, P):
+    """Each output is the same whichever others are asked for."""
+    import torch
+    x = torch.randn(G, C, S, P, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    want = bsi.ess(x, split=True)
+    lib = bsi.get(0)
+    for i in range(3):
+        out = [None, None, None]
+        out[i] = torch.full((G, P), -7.0, device="cuda")
+        lib.check(lib.lib.bsi_ess(lib.h, G, C, S, P, x.data_ptr(), *[None if o is None else o.data_ptr() for o in out],
+                                  None), "bsi_ess")
+        torch.cuda.synchronize()
+        same = torch.equal(out[i], want[i])
+        assert same, i
