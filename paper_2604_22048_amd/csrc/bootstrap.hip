@@ -8,7 +8,7 @@
 //   Lp[r][p] = sum_n C[r][n] E[p][n],  p < 2P over [E+; E-].
 // The product runs on the FP64 matrix cores (v_mfma_f64_16x16x4f64): a
 // workgroup of 4 waves owns a 64 x 64 output tile (16 RT rows for few
-// resamples) of one K split, its waves taking every fourth chunk of 16
+// resamples) of one K split, its waves taking every fourth chunk of 8
 // galaxies; the waves' sums are added through LDS and the partial tile is
 // written; a second kernel adds the splits in order, forms each row's
 // posterior mean of g on the grid, and m_r, c_r; a third takes the standard
@@ -162,6 +162,7 @@ __global__ void __launch_bounds__(256, 2)
 }
 
 constexpr int kMeanThreads = 256;
+constexpr int kAhead = 16;      // splits whose values are on their way together
 
 // Fixed-order block sum of one value per thread (valid in thread 0).
 __device__ __forceinline__ double block_sum(double v, double* red) {
@@ -188,7 +189,10 @@ __device__ __forceinline__ double block_max(double v, double* red) {
   return t;
 }
 
-// One workgroup per row r: the K splits added in order, then for each of
+// One workgroup per row r: the K splits added in order (read in batches: one
+// after another they made a call of few resamples slower than a quarter of the
+// splits did, 30,000 galaxies x 578 columns x 34 rows 264 us against 187, now
+// 131), then for each of
 // the two datasets the posterior mean of g on its grid (gpts, then gpts +
 // 2 P; weights exp(ln P - max)),
 // then m_r = (g+_1 - g-_1) / (2 |g|) - 1 and c_r = (g+_2 + g-_2) / 2.
@@ -202,7 +206,18 @@ __global__ void __launch_bounds__(kMeanThreads) bias_mean_kernel(const double* _
   const int r = blockIdx.x, P2 = 2 * P;
   for (int p = threadIdx.x; p < P2; p += kMeanThreads) {
     double v = 0.0;
-    for (int s = 0; s < n_split; ++s) v += part[((int64_t)s * R + r) * P2 + p];
+    const double* at = part + (int64_t)r * P2 + p;
+    const int64_t step = (int64_t)R * P2;
+    int s = 0;
+    for (; s + kAhead <= n_split; s += kAhead, at += kAhead * step) {
+      double t[kAhead];
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) t[j] = at[j * step];
+      __builtin_amdgcn_sched_barrier(0);     // the loads together, ahead of the adds
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) v += t[j];
+    }
+    for (; s < n_split; ++s, at += step) v += *at;
     lp[p] = v;
   }
   __syncthreads();

@@ -36,3 +36,10 @@ def test_bias_row_tiles(bsi, G, B, n1):
     gm, mc = res["gmean"].cpu().numpy(), res["mc"].cpu().numpy()
     assert np.max(np.abs(gm[0] - gp)) < 1e-10 and np.max(np.abs(gm[1] - gq)) < 1e-10
     assert np.max(np.abs(mc[:, 0] - m)) < 1e-8 and np.max(np.abs(mc[:, 1] - c)) < 1e-10
+
+
+@pytest.mark.parametrize("G,B,n1", [(300, 3, 5), (1003, 17, 6), (9001, 2, 5), (9001, 20, 7), (30011, 1, 4)])
+def test_bias_splits_added(bsi, G, B, n1):
+    """Parts of a split product added in batches and what is left of them: 2, 7, 63
+    and 70 parts, 221."""
+    test_bias_row_tiles(bsi, G, B, n1)
