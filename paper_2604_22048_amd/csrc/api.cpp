@@ -245,6 +245,20 @@ int bsi::hmc_launches(int T, int iters_per_launch, int L, bool nuts, int max_dep
 
 namespace {
 
+// The null stream takes its hardware queue at its first use: here, ahead of the
+// streams of the process's first handle (not beside a capture, which it may
+// not disturb).
+void use_null_stream() {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  hipEvent_t ev = nullptr;
+  if (hipStreamIsCapturing(nullptr, &st) == hipSuccess && st == hipStreamCaptureStatusNone &&
+      hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess) {
+    (void)hipEventRecord(ev, nullptr);
+    (void)hipEventDestroy(ev);
+  }
+  (void)hipGetLastError();
+}
+
 // Every workspace buffer of a handle (an array: an initializer_list returned
 // from a function would refer to a temporary that dies with the return).
 std::array<DevBuf*, 14> all_buffers(bsi_handle h) {
@@ -321,6 +335,7 @@ int bsi_create(bsi_handle* out, int32_t device, const char* tune_cache) {
     g_create_error = "hipSetDevice failed";
     return BSI_EHIP;
   }
+  use_null_stream();
   // the allocation-free entry point's scratch: this device's address of the
   // library's device array, looked up once per device with the device current
   void* scratch = nullptr;
@@ -360,11 +375,13 @@ int bsi_create(bsi_handle* out, int32_t device, const char* tune_cache) {
          hipEventCreateWithFlags(&h->ev_join[i], hipEventDisableTiming) == hipSuccess;
   // A process has four hardware queues; a new stream takes the one with the
   // fewest streams, the youngest of several.  The null stream holds the first
-  // queue, the auxiliary streams now hold the other three, and the handle's own
-  // stream is to share the null stream's, so that a fork from either runs its
-  // four branches on four queues: as many short-lived streams come before it.
-  // (With `own` created first two auxiliary streams shared a queue, and a
-  // round of five stamp sides ended 0.9 ms later than its longest side.)
+  // queue (use_null_stream), the auxiliary streams now hold the other three, and
+  // the handle's own stream is to share the null stream's, so that a fork from
+  // either runs its four branches on four queues: as many short-lived streams
+  // come before it.  (With `own` created first two auxiliary streams shared a
+  // queue, and a round of five stamp sides ended 0.9 ms later than its longest
+  // side; with no queue taken by the null stream yet `own` shared one with an
+  // auxiliary stream, and up to 1.8 times as long passed.)
   hipStream_t fill[kAuxStreams] = {};
   for (int i = 0; ok && i < kAuxStreams; ++i)
     ok = hipStreamCreateWithFlags(&fill[i], hipStreamNonBlocking) == hipSuccess;
