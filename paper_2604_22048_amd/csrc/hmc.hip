@@ -1648,9 +1648,13 @@ static bool launch_fixed_nuts(const HmcArgs& a, int grid, size_t lds, hipStream_
 // whose lane columns split (team_waves).  Under NUTS, where every point also
 // carries its bookkeeping, from 53 px on (16 transitions of 32 galaxies, C = 4:
 // 25 px 0.60 ms by teams and by one wave, 41 px 0.79 and 0.78, 53 px 0.91 and
-// 1.05, 73 px 0.75 and 0.89, 101 px 0.94 and 1.22).
+// 1.05, 73 px 0.75 and 0.89, 101 px 0.94 and 1.22).  Fixed-length trajectories of a
+// single chain from 41 px on: at 25 px a wave's whole evaluation is 1.03 us, a
+// team's 1.10 (116 galaxies 596 us by one wave, 675 by teams).  Another plan than
+// the default one (bsi_autotune, which measures full launches, or bsi_set_plan)
+// keeps one wave.
 constexpr bool team_plan(int N, int P, int H, bool nuts) {
-  return (N & 1) && P == make_slot_plan(N).P && team_waves(P * H) > 1 &&
+  return (N & 1) && P == make_slot_plan(N).P && team_waves(P * H) > 1 && (H > 1 || N >= 41) &&
          (H == 1 || paired_chains_plan(N, P)) && (H < 4 || quad_chains_plan(N, P)) &&
          (!nuts || (N >= 53 && H <= 2));
 }
