@@ -637,17 +637,19 @@ int bsi_hmc_sample(bsi_handle h, const bsi_batch* batch, const float* data, cons
   a.off = static_cast<const int64_t*>(h->off.p);
   a.nuts = nuts ? 1 : 0;
   a.max_depth = cfg->max_tree_depth;
-  auto waves = [&](const ClassRange& c) {      // per chain
-    return (mx || nuts) ? 1 : hmc_split_waves(c.N, C, c.P, batch->profile, cfg->waves_per_chain);
-  };
-  for (const ClassRange& c : p.classes) {
+  // the launches of a class
+  auto args = [&](const ClassRange& c) {
     HmcArgs ac = a;
     ac.N = c.N;
     ac.P = c.P;
-    ac.wpc = waves(c);
+    ac.gidx = ggidx_ptr(h, p, c);
     ac.n_gal = c.gcount;
-    a.side_waves += hmc_team_waves(ac);
-  }
+    ac.wpc = (mx || nuts) ? 1 : hmc_split_waves(c.N, C, c.P, batch->profile, cfg->waves_per_chain);
+    return ac;
+  };
+  int64_t side_waves = 0;
+  for (const ClassRange& c : p.classes) side_waves += hmc_team_waves(args(c));
+  a.side_waves = side_waves;
 
   const int T = a.t_stop;
   const bool plain = cfg->form == BSI_FORM_PLAIN;
@@ -656,11 +658,9 @@ int bsi_hmc_sample(bsi_handle h, const bsi_batch* batch, const float* data, cons
   hipError_t e = for_classes(h, p, s, cap, [&](const ClassRange& c, hipStream_t st) -> hipError_t {
     hipError_t x = class_spectrum(h, p, c, data, nullptr, nullptr, st);
     if (x == hipSuccess && mx) x = class_weights(h, batch, p, c, st);
-    HmcArgs ac = a;
-    ac.N = c.N;
-    ac.P = c.P;
-    ac.gidx = ggidx_ptr(h, p, c);
-    ac.n_gal = c.gcount;
+    HmcArgs ac = args(c);
+    const int wpc = ac.wpc;
+    ac.wpc = 1;
     ac.n_steps = 0;
     if (x == hipSuccess) x = launch_hmc_init(ac, c.gcount, st);
     if (plain) {
@@ -672,7 +672,7 @@ int bsi_hmc_sample(bsi_handle h, const bsi_batch* batch, const float* data, cons
           x = launch_hmc_advance(ac, 1, st);
       return x;
     }
-    ac.wpc = waves(c);
+    ac.wpc = wpc;
     for (int k = 0; x == hipSuccess && k < n_launch; ++k) {
       // evenly sized launches: iterations [k T / n, (k + 1) T / n)
       const int it = (int)((int64_t)(k + 1) * T / n_launch - (int64_t)k * T / n_launch);
@@ -680,7 +680,7 @@ int bsi_hmc_sample(bsi_handle h, const bsi_batch* batch, const float* data, cons
       x = launch_hmc_advance(ac, c.gcount, st);
     }
     return x;
-  }, [&](const ClassRange& c) { return chain_cost(c.N, waves(c)) * std::max(1.0, c.gcount / 512.0); });
+  }, [&](const ClassRange& c) { return hmc_launch_us(args(c)); });
   if (e != hipSuccess) return hip_fail(h, e, "hmc launch");
   e = launch_hmc_finalize(static_cast<const ChainState*>(h->state.p), batch->n_gal, C, cfg->n_samples,
                           chain_stats, status, s);

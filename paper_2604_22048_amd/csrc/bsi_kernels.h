@@ -185,10 +185,20 @@ int hmc_launches(int T, int iters_per_launch, int L, bool nuts, int max_depth);
 // Whether the advance kernel with exposures / noise weights (mx) runs on the
 // kernels specialised for stamp side N: one wave per chain, the exponential or
 // Spergel profile and P N's default plan with a specialised kernel.
+// Whether the advance kernel with exposures / noise weights (mx) runs on the
+// kernels specialised for stamp side N: one wave per chain, the exponential or
+// Spergel profile and P N's default plan with a specialised kernel.
+bool hmc_mx_fixed(int N, int P, int prof, int wpc);
 // Waves of an advance launch if its chain groups are evaluated by teams, where
 // there is a team kernel (a.side_waves decides whether they are).
 int64_t hmc_team_waves(const HmcArgs& a);
-bool hmc_mx_fixed(int N, int P, int prof, int wpc);
+// Whether an advance launch of several steps is one by teams.
+bool hmc_runs_teams(const HmcArgs& a);
+// Duration of an evaluation of a galaxy's chains alone, and per evaluation of an
+// advance launch, us, about: what a call's launches are placed on streams by.
+enum class EvalForm : int { kGeneral, kFixed, kTeam };      // (kFixed: the kernels of one side)
+double hmc_eval_us(int N, int C, int n_exp, int wpc, EvalForm form);
+double hmc_launch_us(const HmcArgs& a);
 // Slot plans with a trajectory kernel specialised for stamp side N (0-terminated list of P).
 const int* hmc_fixed_plans(int N);
 hipError_t launch_hmc_init(const HmcArgs& a, int grid, hipStream_t s);

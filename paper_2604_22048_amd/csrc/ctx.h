@@ -288,14 +288,6 @@ inline int stage_upload(bsi_handle h, hipStream_t s, bool cap, std::initializer_
   return BSI_OK;
 }
 
-// Duration of a chain's evaluation on side N by W waves, to a factor: its pairs
-// per wave beside what does not depend on the side (one wave: 1.2 us at 25 px,
-// 2.2 at 101, one chain a group).  Galaxies that fit the device side by side
-// take no longer than one (512 of four chains), so a size's duration does not
-// follow its share of the work: 400 galaxies of five sides under NUTS 1.92 ms
-// with the shares, 1.77 so (the one mix this rests on).
-inline double chain_cost(int N, int W) { return (double)N * N / W + 10000.0; }
-
 // Enqueue fn(i, stream) for i = 0..n-1 on s and the handle's auxiliary
 // streams (at most kForkStreams streams in all), forked from and joined back
 // into s by events, so that the launches of different size classes run

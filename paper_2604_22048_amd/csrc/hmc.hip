@@ -1710,10 +1710,44 @@ static bool launch_team(const HmcArgs& a, int H, hipStream_t s) {
   return false;
 }
 
+// Whether there is a team kernel for the launch.
+static bool has_team(const HmcArgs& a, int H) {
+  if (a.mx || a.wpc != 1 || a.C > 4 || a.prof == kProfGauss || !team_plan(a.N, a.P, H, a.nuts)) return false;
+  for (const int* p = hmc_fixed_plans(a.N); *p; ++p)
+    if (*p == a.P) return true;
+  return false;
+}
+
 int64_t hmc_team_waves(const HmcArgs& a) {
   const int H = launch_chains_per_wave(a, false);
-  const bool team = !a.mx && a.wpc == 1 && a.C <= 4 && a.prof != kProfGauss && team_plan(a.N, a.P, H, a.nuts);
-  return (int64_t)a.n_gal * (a.C / H) * (team ? team_waves(a.P * H) : a.wpc);
+  return (int64_t)a.n_gal * (a.C / H) * (has_team(a, H) ? team_waves(a.P * H) : a.wpc);
+}
+
+bool hmc_runs_teams(const HmcArgs& a) {
+  const int H = launch_chains_per_wave(a, false);
+  return a.side_waves <= team_side_waves(a.nuts) && has_team(a, H) &&
+         (int64_t)a.n_gal * (a.C / H) <= team_groups(a.N, a.P, H, a.nuts);
+}
+
+// One galaxy's chains, us: by teams 1.1 (25 px) to 2.2 (101); on the specialised
+// sides by one wave a chain group 1.3 (41 px, one chain), 2.6 at 53, 3.6 at 73, 5.3
+// at 101; on others 1.7 up to 32 px, 2.7 at 48, 4.0 at 64, 5.2 at 80, 7.2 at 115, 7.9
+// at 127, five to eight chains 2.8, 3.7, 5.1, 6.8, 9.2, 10; two exposures up to twice
+// as long.
+double hmc_eval_us(int N, int C, int n_exp, int wpc, EvalForm form) {
+  if (form == EvalForm::kTeam) return 1.1 + 0.0115 * N;
+  const double us = form == EvalForm::kFixed ? std::max(1.2, 0.041 * N)
+                                             : std::max(C > 4 ? 2.3 : 1.7, (C > 4 ? 0.075 : 0.058) * N);
+  return us * n_exp / wpc;
+}
+
+double hmc_launch_us(const HmcArgs& a) {
+  bool fixed = false;
+  for (const int* p = hmc_fixed_plans(a.N); *p; ++p) fixed |= *p == a.P;
+  fixed &= a.C <= 4 && a.prof != kProfGauss;
+  const EvalForm form = hmc_runs_teams(a) ? EvalForm::kTeam : fixed ? EvalForm::kFixed : EvalForm::kGeneral;
+  const double waves = (double)a.n_gal * (a.C / launch_chains_per_wave(a, false)) * a.wpc;
+  return hmc_eval_us(a.N, a.C, a.n_exp, a.wpc, form) * std::max(1.0, waves / 1536.0);
 }
 
 template <int PROF, bool INIT>
@@ -1780,8 +1814,7 @@ static hipError_t launch_impl(const HmcArgs& a, int grid, hipStream_t s) {
   // teams, in place of the specialised one-wave kernels (C <= 4; more chains run
   // on the general ones, which may round otherwise); single steps stay with one
   // wave: staging would dominate
-  if (!INIT && !a.mx && a.wpc == 1 && a.C <= 4 && a.n_steps > 1 && a.prof != kProfGauss &&
-      a.side_waves <= team_side_waves(a.nuts) &&
+  if (!INIT && a.n_steps > 1 && hmc_runs_teams(a) &&
       (a.prof == kProfExp ? launch_team<kProfExp>(a, H, s) : launch_team<kProfSpergel>(a, H, s)))
     return hipGetLastError();
   const size_t lds = a.mx ? hmc_lds_bytes(a.N, a.C, a.P, 1, H, a.n_exp, true, a.nuts)

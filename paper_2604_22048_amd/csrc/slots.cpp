@@ -496,14 +496,17 @@ int bsi_slots_advance(bsi_slots sv, int32_t n_iter) {
     }
   }
   HmcArgs base = base_args(sv);
-  for (int i : active) {
+  auto args = [&](int i) {
     HmcArgs a = base;
     a.N = sv->cls[i].N;
     a.P = sv->cls[i].P;
     a.wpc = sv->cls[i].W;
     a.n_gal = (int)sv->cls[i].resident.size();
-    base.side_waves += hmc_team_waves(a);
-  }
+    return a;
+  };
+  int64_t side_waves = 0;
+  for (int i : active) side_waves += hmc_team_waves(args(i));
+  base.side_waves = side_waves;
   e = fork_join(h, sv->s, (int)active.size(), [&](int j, hipStream_t st) -> hipError_t {
     const int i = active[j];
     const SizeClass& k = sv->cls[i];
@@ -524,22 +527,15 @@ int bsi_slots_advance(bsi_slots sv, int32_t n_iter) {
       x = launch_hmc_init(a, a.n_gal, st);
       if (x != hipSuccess) return x;
     }
-    HmcArgs a = base;
-    a.N = k.N;
-    a.P = k.P;
-    a.wpc = k.W;
+    HmcArgs a = args(i);
     a.gidx = res;
-    a.n_gal = (int)k.resident.size();
     a.n_steps = iters[i] * sv->L;
     if (sv->cfg.pace && (x = hipEventRecord(k.ev_beg, st)) != hipSuccess) return x;
     x = launch_hmc_advance(a, a.n_gal, st);
     if (x == hipSuccess && sv->cfg.pace) x = hipEventRecord(k.ev_end, st);
     return x;
   }, [&](int j) {
-    // a launch's duration follows one request's chain (the requests of a
-    // size run side by side), times its iterations
-    const SizeClass& k = sv->cls[active[j]];
-    return chain_cost(k.N, k.W) * iters[active[j]];
+    return hmc_launch_us(args(active[j])) * iters[active[j]];
   });
   if (e != hipSuccess) return hip_fail(h, e, "advance launch");
   if (sv->ess) {
