@@ -285,9 +285,9 @@ typedef struct {
   int32_t form;              /* BSI_FORM_BATCHED: all galaxies per launch;
                                 BSI_FORM_PLAIN: one galaxy and one leapfrog step per launch */
   int32_t iters_per_launch;  /* batched form: trajectories per kernel launch at least (>= 1);
-                                the library takes more where they end within 512 evaluations
-                                of a chain (a NUTS transition: up to 2^max_tree_depth); the
-                                samples do not depend on it                                 */
+                                the library takes more where they end within about 512
+                                evaluations of a chain (a NUTS transition counted as
+                                2^(max_tree_depth - 1)); the samples do not depend on it    */
   int32_t use_graph;         /* accepted and without effect: a call's launches are few enough
                                 to be enqueued directly, the stamp sizes concurrently on
                                 forked streams                                             */

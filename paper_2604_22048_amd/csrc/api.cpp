@@ -235,10 +235,13 @@ constexpr int kLaunchEvals = 512;
 }  // namespace
 
 // A launch's iterations are at most iters_per_launch (which may be the largest
-// int) or those that take kLaunchEvals evaluations at most, a NUTS transition
-// up to 2^max_depth; and its steps fit an int.
+// int) or those that take about kLaunchEvals evaluations, a NUTS transition
+// counted as half of its 2^max_depth at most (with the whole of it, eight
+// doublings took 33 ms in launches of two transitions, 18 in launches of many,
+// 42 in launches of one: a galaxy's workgroup ends with its slowest chain); and
+// its steps fit an int.
 int bsi::hmc_launches(int T, int iters_per_launch, int L, bool nuts, int max_depth) {
-  int most = std::max({iters_per_launch, 1, nuts ? kLaunchEvals >> max_depth : kLaunchEvals / L});
+  int most = std::max({iters_per_launch, 1, nuts ? kLaunchEvals >> (max_depth - 1) : kLaunchEvals / L});
   most = std::min(most, nuts ? T : std::min(T, INT32_MAX / L));
   return T > 0 ? (int)(((int64_t)T + most - 1) / most) : 0;
 }
