@@ -150,7 +150,7 @@ __device__ __forceinline__ double potential(const GalCtx& c, const Cols& lc, con
     fill_team(lc, c.g, c.X, c.Ym, F, dx, dy);
     const KSums S =
         kspace_sums_team<PROF, P, CHI2, NFIX, H>(lc, c.cols, c.dh, c.X, c.Ym, sh, c.team, c.part);
-    r = kspace_finish<PROF, true>(S, sh, F, s, e1, e2, c.norm);
+    r = kspace_finish<PROF>(S, sh, F, s, e1, e2, c.norm);
   } else {
     fill_tables<H>(c.g, c.sp, c.atab, c.X, c.Ym, c.Yf, F, dx, dy);
     KSums S;

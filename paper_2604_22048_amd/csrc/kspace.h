@@ -1061,10 +1061,10 @@ __device__ __forceinline__ KSums kspace_sums_team(const TeamCols<NFIX, P, H, RES
 // Turn the sums into log L and d log L / d(F, s, e1, e2, dx, dy).
 // norm = 1 / (N^2 sigma^2); s_arcsec is the half-light radius.  The X table
 // carried the flux, so sF = sum Re(conj R T) and dT/dF = T / F.
-// FUSED: the sums of two products rounded as the compiler fuses them in the
-// kernels of one wave per chain group, spelled out; which product of a sum it
-// fuses is its own choice in each kernel, and a team's draws are to be theirs.
-template <int PROF, bool FUSED = false>
+// The sums of two products are written out as they are fused: which product of a
+// sum a compiler fuses is its own choice in each kernel, and a team's draws are
+// to be those of one wave.
+template <int PROF>
 __device__ __forceinline__ KResult kspace_finish(const KSums& S, const Shape& sh, float F,
                                                  float s_arcsec, float e1, float e2, float norm) {
   KResult r;
@@ -1073,15 +1073,9 @@ __device__ __forceinline__ KResult kspace_finish(const KSums& S, const Shape& sh
   const float n2 = 2.0f * norm;                  // the halved sums doubled
   r.dF = n2 * S.sF * rcp_nr(F);
   r.ds = n2 * (2.0f * c * rcp_nr(s_arcsec)) * S.sq;
-  if constexpr (FUSED) {
-    r.de1 = n2 * c * sh.inv1mE *
-            fmaf(2.0f * e1, S.sq, fmaf(2.0f * e1 + 2.0f, S.sxx, (2.0f * e1 - 2.0f) * S.syy));
-    r.de2 = n2 * c * sh.inv1mE * fmaf(2.0f * e2, S.sq, fmaf(2.0f * e2, S.sxx + S.syy, 4.0f * S.sxy));
-  } else {
-    r.de1 = n2 * c * sh.inv1mE *
-            ((2.0f * e1 + 2.0f) * S.sxx + (2.0f * e1 - 2.0f) * S.syy + 2.0f * e1 * S.sq);
-    r.de2 = n2 * c * sh.inv1mE * (2.0f * e2 * (S.sxx + S.syy) + 4.0f * S.sxy + 2.0f * e2 * S.sq);
-  }
+  r.de1 = n2 * c * sh.inv1mE *
+          fmaf(2.0f * e1, S.sq, fmaf(2.0f * e1 + 2.0f, S.sxx, (2.0f * e1 - 2.0f) * S.syy));
+  r.de2 = n2 * c * sh.inv1mE * fmaf(2.0f * e2, S.sq, fmaf(2.0f * e2, S.sxx + S.syy, 4.0f * S.sxy));
   r.ddx = n2 * S.sdx;
   r.ddy = n2 * S.sdy;
   return r;
