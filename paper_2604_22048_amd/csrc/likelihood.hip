@@ -40,6 +40,18 @@ __host__ __device__ inline LoglikLds loglik_lds(int N, int P, bool mx, bool fuse
   return l;
 }
 
+// Waves per SIMD that a form's registers leave room for.  One unit without
+// weights: four, under whose 128 registers the contraction spills 4 to 36 where
+// three would take 146 and spill none, but hide less (10,000 stamps of 53 px 185
+// against 195 us, 41 px 132 against 143).  With weights, which would spill 46 to 56
+// (two units: 89 and more): three (8 to 12 left; 10,000 of 53 px 290 -> 252 us, 700
+// of three exposures 70 -> 63).  Two units: two, whose workgroups of eight waves
+// LDS mostly leaves room for one of anyway; no spills (300 bytes a lane before;
+// 700 of 73 px with weights 96 -> 67 us, 700 of 101 px 103 -> 93).
+constexpr int loglik_simd_waves(int P, bool mx, int U) {
+  return U == 0 ? 1 : P > 4 || U == 2 ? 2 : mx ? 3 : 4;
+}
+
 // MX: the sum over the galaxy's n_exp exposures (stamps gal n_exp + j, each
 // transformed in turn) with per-bin noise weights (Appendix C).
 // U units of the transform per wave (dft_per_wave), or U = 0: the spectra come
@@ -47,11 +59,11 @@ __host__ __device__ inline LoglikLds loglik_lds(int N, int P, bool mx, bool fuse
 // Bound by the matrix cores (the transform's products, half of the time) and by
 // what runs beside them: 4 workgroups of 4 waves per compute unit at 53 px,
 // some contracting with one wave while the others transform.  10,000 galaxies
-// of 53 px: the call 183 us; transform and contraction as two kernels, with
+// of 53 px: the call 185 us; transform and contraction as two kernels, with
 // the transform's factors looked up per element and the spectra (123 MB)
 // through memory and LDS, took 218 and 69.
 template <int PROF, bool RESID, int P, bool MX, int U>
-__global__ void __launch_bounds__(U == 0 ? kWave : 512, U == 0 ? 1 : P <= 4 ? 4 : 2) loglik_kernel(LoglikArgs a) {
+__global__ void __launch_bounds__(U == 0 ? kWave : 512, loglik_simd_waves(P, MX, U)) loglik_kernel(LoglikArgs a) {
   static_assert(!(MX && RESID), "exposures: k-space form only");
   extern __shared__ float4 smem4[];
   __shared__ double red[8];
@@ -160,7 +172,7 @@ template <int PROF, bool RESID, bool MX, int U>
 void launch_loglik_u(const LoglikArgs& a, hipStream_t s) {
   const size_t lds = loglik_lds(a.N, a.P, MX, U > 0).total;
   const int nw = U > 0 ? dft_waves(a.N) : 1;
-  const dim3 grid(U > 0 ? dft_grid(a.n, nw, lds, a.P <= 4 ? 4 : 2) : a.n), block(kWave * nw);
+  const dim3 grid(U > 0 ? dft_grid(a.n, nw, lds, loglik_simd_waves(a.P, MX, U)) : a.n), block(kWave * nw);
   auto go = [&](auto kern) {
     if (lds > 64 * 1024)
       (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -186,7 +198,7 @@ void launch_loglik_p(const LoglikArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// One kernel wherever its waves hold one unit of the transform (up to 64 px):
+// One kernel wherever its waves hold one unit of the transform (up to 63 px):
 // 53 px, 1 stamp 19 us against 32 in two kernels, 1,000 27 / 44, 10,000 183 /
 // 184 (calls, host included).  Larger stamps leave one or two of its
 // workgroups per compute unit, which idle while one wave contracts: 73 px,
