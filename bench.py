@@ -587,8 +587,7 @@ def uneven_leg(api, torch, stream, n_gal, log=None, per_size_runs=True, oracle=N
     """Batched uneven workload: n_gal galaxies, stamp side from the size rule
     (25-101), PSF FWHM ~ U(0.6, 0.9), SNR 10-200, 4 chains, 20 leapfrog
     steps, 300 warmup + 1000 draws.  The sizes run concurrently on
-    forked streams; the run with use_graph set (graph_form) repeats it, since
-    the sampler now enqueues its launches directly either way.  per_size_runs: also time each size class alone
+    forked streams.  per_size_runs: also time each size class alone
     (uneven_per_size)."""
     cfg = gen.CONFIGS["uneven"]
     say = log or (lambda m: None)
@@ -600,24 +599,18 @@ def uneven_leg(api, torch, stream, n_gal, log=None, per_size_runs=True, oracle=N
     hcfg = api.HmcConfig(n_chains=C, n_leapfrog=L, n_warmup=W, n_samples=S, adapt=True,
                          metric=api.N.METRIC_FISHER, step_size=0.5, target_accept=0.8, jitter=0.2,
                          use_graph=True, seed=gen.chain_seed(cfg.index))
-    dcfg = api.HmcConfig(**{**hcfg.__dict__, "use_graph": False})
-    run = lambda cfg_, n_s, want: api.hmc_sample(b, data, ref, init,
-                                                 api.HmcConfig(**{**cfg_.__dict__, "n_samples": n_s}),
-                                                 want_samples=want)
-    run(hcfg, 0, False)                                                # warm
-    run(dcfg, 0, False)
-    (smp, st, status), t_hmc = timed(torch, lambda: run(dcfg, S, True), stream)
-    say(f"[uneven] sampler call {t_hmc:.3f} s (direct)")
+    run = lambda n_s, want: api.hmc_sample(b, data, ref, init,
+                                           api.HmcConfig(**{**hcfg.__dict__, "n_samples": n_s}),
+                                           want_samples=want)
+    run(0, False)                                                      # warm
+    (smp, st, status), t_hmc = timed(torch, lambda: run(S, True), stream)
+    say(f"[uneven] sampler call {t_hmc:.3f} s")
     (e, rh), _ = timed(torch, lambda: api.ess(smp), stream)
-    _, t_w = timed(torch, lambda: run(dcfg, 0, False), stream)
-    _, t_hmc_g = timed(torch, lambda: run(hcfg, S, True), stream)
-    _, t_w_g = timed(torch, lambda: run(hcfg, 0, False), stream)
-    say(f"[uneven] sampler call {t_hmc_g:.3f} s (graph)")
+    _, t_w = timed(torch, lambda: run(0, False), stream)
     n_eff = float(e.mean(dim=1).mean())
     acc = st[..., 0].mean()
     n_flag = int((status != 0).sum())
     tpg = t_w / n_gal + (t_hmc - t_w) / (n_gal * n_eff) * TARGET_ESS
-    tpg_g = t_w_g / n_gal + (t_hmc_g - t_w_g) / (n_gal * n_eff) * TARGET_ESS
     counts = {int(N): int(np.sum(t.n_pix == N)) for N in np.unique(t.n_pix)}
     flop = sum(flops_per_eval(N) * k for N, k in counts.items()) * C * L * (W + S)
     del smp, st, e, rh, data
@@ -629,8 +622,6 @@ def uneven_leg(api, torch, stream, n_gal, log=None, per_size_runs=True, oracle=N
            "galaxies_per_s": round(1.0 / tpg, 1),
            "achieved_tflops": round(flop / t_hmc / 1e12, 3),
            "frac_fp32_peak": round(flop / t_hmc / 1e12 / FP32_PEAK_TFLOPS, 4),
-           "graph_form": {"t_hmc_s": round(t_hmc_g, 4), "t_warmup_s": round(t_w_g, 4),
-                          "galaxies_per_s": round(1.0 / tpg_g, 1)},
            "accept_rate": round(float(acc), 4),
            "status_nonzero": n_flag,
            "per_size": per_size}
