@@ -524,7 +524,10 @@ int bsi_shear_hmc(bsi_handle h, int32_t n_gal, int32_t K, const float* e1p, cons
  * number of chains up to 4): four (16 lanes each, one wave per galaxy) for
  * fixed-length trajectories of exactly four chains (one exposure, white
  * noise), else two (32 lanes each); one chain per wave otherwise.  The choice
- * depends only on the size, plan and configuration, never on the batch. */
+ * depends only on the size, plan and configuration, never on the batch.  Small
+ * launches (white noise, one wave per chain requested, the default plans of 25,
+ * 41, 53, 73 and 101 px) further spread a wave's chains over two to four waves
+ * where that ends sooner; the draws are the same bit for bit. */
 
 /* Set (P > 0) or reset to the default (P = 0) the slot plan of stamp side n.
  * BSI_EINVAL unless 8 <= n <= 128 and P is 0 or one of 1, 2, 3, 4, 5, 6, 8

@@ -21,6 +21,10 @@
 namespace bsi {
 
 constexpr int kWave = 64;
+// Wait counters (gfx9 encoding): all vector memory operations done; all LDS
+// operations done.
+constexpr int kWaitVmcnt0 = 0x0F70;
+constexpr int kWaitLgkmcnt0 = 0xC07F;
 constexpr int kMaxN = 128;
 constexpr float kPiF = 3.14159265358979323846f;
 constexpr double kLn10 = 2.30258509299404568402;

@@ -293,7 +293,8 @@ inline int stage_upload(bsi_handle h, hipStream_t s, bool cap, std::initializer_
 // into s by events, so that the launches of different size classes run
 // concurrently.  cost(i) estimates item i's duration: the items are enqueued
 // in descending cost, each on the stream with the least estimated cost so
-// far, so the longest runs on s and the shortest share a stream.  Used
+// far, so the longest runs on s and the shortest share a stream.  The
+// callers decide whether the fork is worth its host time.  Used
 // outside stream capture only: a capture of the fork (with the executable
 // kept alive until its replays had run) still ended in a host segmentation
 // fault inside the call, so every capture records the launches in sequence

@@ -111,8 +111,6 @@ __device__ __forceinline__ void dft_row_bases(int N, const SlotPlan& sp, int* ro
   for (int v = threadIdx.x; v < 16 * dft_dims(N).nrb; v += blockDim.x) rows[v] = v / sp.R * sp.P * 64 + v % sp.R * npc;
 }
 
-constexpr int kWaitVmcnt0 = 0x0F70;   // every vector memory operation done (gfx9 wait counter)
-
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(kWaitVmcnt0); }
 
 // Load stamp `data` (minus `model`, both at the stamp's first pixel) into d and

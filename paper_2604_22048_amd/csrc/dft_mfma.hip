@@ -189,6 +189,8 @@ __device__ __forceinline__ double profile_g(int prof, float nu, double r2, doubl
 // unfolded, with the factors looked up and their table built per stamp), 1,000
 // of 101 px 65 us (284); float64 with the likelihood, 1,000 of 41 px 57 us, one
 // of 101 px 74 us (direct float64 sums, a row of the spectrum at a time: 291, 822).
+// The float64 form of three units (the largest sides) spills 72 of its 256
+// registers, the most that a workgroup of eight waves can have.
 template <typename T, int U>
 __global__ void __launch_bounds__(512, sizeof(T) == 4 && U == 1 ? 4 : 2) render_mfma_kernel(
     const float* __restrict__ params, const float* __restrict__ psf_fwhm, const int32_t* __restrict__ gidx, int n,

@@ -38,7 +38,6 @@ constexpr int kMaxWaves = 8;       // waves per series
 constexpr int kSide = 4;           // blocks of 16 lags side by side at most
 constexpr int kEssChains = 16;     // chains at most
 constexpr int kXcds = 8;
-constexpr int kWaitVmcnt0 = 0x0F70;   // every vector memory operation done (gfx9 wait counter)
 
 // LDS floats of n draws: the lanes read up to a window past the last one
 // (masked), the transfer writes up to a wave.

@@ -1676,7 +1676,11 @@ constexpr int team_groups(int N, int P, int H, bool nuts) {
 // Waves of all the launches side by side: mixed batches of five sides, C = 4, 16
 // iterations: 400 galaxies (2,000 waves) 1.49 ms by teams and 2.48 by one wave,
 // 600 (3,000) 2.12 and 2.50; under NUTS, whose chains end one by one, 400 (1,600)
-// 1.76 and 1.87, 600 (with every side in teams, 3,400) 2.46 and 1.91.
+// 1.76 and 1.87, 600 (with every side in teams, 3,400) 2.46 and 1.91.  Where the
+// two meet for fixed lengths depends on the mix: with as many galaxies of each
+// side and 20 iterations at 1,000 galaxies of four chains (2.92 and 2.98 ms;
+// 1,300: 3.64 and 3.25), at 600 of two chains (1.79 and 1.77); mostly small sides
+// between 800 (2.20 and 2.55) and 1,300 (3.47 and 2.71).  3,072 waves is under all.
 constexpr int team_side_waves(bool nuts) { return nuts ? 2048 : 3072; }
 
 template <int PROF, int NN, int PP, int H, bool NUTS>

@@ -265,10 +265,6 @@ __device__ __forceinline__ float wave_lw_max(const Point& P, float emax2, const 
   return wave_max_dpp(m);
 }
 
-// Wait counters (gfx9 encoding): all vector memory operations done; all LDS
-// operations done.
-constexpr int kWaitVmcnt0 = 0x0F70;
-constexpr int kWaitLgkmcnt0 = 0xC07F;
 // A point whose total weight against the bound falls below this is evaluated
 // again against its exact maximum (weights below 2^-126 of the bound would
 // have underflowed).
