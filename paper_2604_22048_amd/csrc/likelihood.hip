@@ -45,11 +45,15 @@ __host__ __device__ inline LoglikLds loglik_lds(int N, int P, bool mx, bool fuse
 // three would take 146 and spill none, but hide less (10,000 stamps of 53 px 185
 // against 195 us, 41 px 132 against 143).  With weights, which would spill 46 to 56
 // (two units: 89 and more): three (8 to 12 left; 10,000 of 53 px 290 -> 252 us, 700
-// of three exposures 70 -> 63).  Two units: two, whose workgroups of eight waves
-// LDS mostly leaves room for one of anyway; no spills (300 bytes a lane before;
-// 700 of 73 px with weights 96 -> 67 us, 700 of 101 px 103 -> 93).
+// of three exposures 70 -> 63).  Two units, whose workgroups of eight waves LDS
+// mostly leaves room for one of: three as well, which keeps room for another
+// side's four waves beside them (up to 15 left, 38 with weights, where 300 bytes a
+// lane were spilled; 700 of 73 px with weights 96 -> 74 us, 700 of 101 px 103 -> 94).
+// Two would spill none and take 5 to 15 % less for a side alone with weights (700
+// of 73 px 66), but mixed batches up to 15 % more (1,000 galaxies of 32, 48 and
+// 64 px, three exposures: 220 against 192).
 constexpr int loglik_simd_waves(int P, bool mx, int U) {
-  return U == 0 ? 1 : P > 4 || U == 2 ? 2 : mx ? 3 : 4;
+  return U == 0 ? 1 : P > 4 ? 2 : U == 2 || mx ? 3 : 4;
 }
 
 // MX: the sum over the galaxy's n_exp exposures (stamps gal n_exp + j, each
@@ -59,7 +63,7 @@ constexpr int loglik_simd_waves(int P, bool mx, int U) {
 // Bound by the matrix cores (the transform's products, half of the time) and by
 // what runs beside them: 4 workgroups of 4 waves per compute unit at 53 px,
 // some contracting with one wave while the others transform.  10,000 galaxies
-// of 53 px: the call 185 us; transform and contraction as two kernels, with
+// of 53 px: 185 us a call, calls queued back to back; transform and contraction as two kernels, with
 // the transform's factors looked up per element and the spectra (123 MB)
 // through memory and LDS, took 218 and 69.
 template <int PROF, bool RESID, int P, bool MX, int U>
