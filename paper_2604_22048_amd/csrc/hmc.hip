@@ -1751,7 +1751,8 @@ double hmc_launch_us(const HmcArgs& a) {
   fixed &= a.C <= 4 && a.prof != kProfGauss;
   const EvalForm form = hmc_runs_teams(a) ? EvalForm::kTeam : fixed ? EvalForm::kFixed : EvalForm::kGeneral;
   const double waves = (double)a.n_gal * (a.C / launch_chains_per_wave(a, false)) * a.wpc;
-  return hmc_eval_us(a.N, a.C, a.n_exp, a.wpc, form) * std::max(1.0, waves / 1536.0);
+  // (n_exp is set with mx only)
+  return hmc_eval_us(a.N, a.C, a.mx ? a.n_exp : 1, a.wpc, form) * std::max(1.0, waves / 1536.0);
 }
 
 template <int PROF, bool INIT>
