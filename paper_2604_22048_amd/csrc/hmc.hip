@@ -1737,12 +1737,13 @@ bool hmc_runs_teams(const HmcArgs& a) {
 // sides by one wave a chain group 1.3 (41 px, one chain), 2.6 at 53, 3.6 at 73, 5.3
 // at 101; on others 1.7 up to 32 px, 2.7 at 48, 4.0 at 64, 5.2 at 80, 7.2 at 115, 7.9
 // at 127, five to eight chains 2.8, 3.7, 5.1, 6.8, 9.2, 10; two exposures up to twice
-// as long.
+// as long.  A chain over W waves 1.6 (41 px) to 2.9 (101) with W = 4, 1.6 to 4.1 with 2.
 double hmc_eval_us(int N, int C, int n_exp, int wpc, EvalForm form) {
   if (form == EvalForm::kTeam) return 1.1 + 0.0115 * N;
-  const double us = form == EvalForm::kFixed ? std::max(1.2, 0.041 * N)
-                                             : std::max(C > 4 ? 2.3 : 1.7, (C > 4 ? 0.075 : 0.058) * N);
-  return us * n_exp / wpc;
+  const double us = wpc > 1                    ? 1.5 + 4.1e-4 * N * N / wpc
+                    : form == EvalForm::kFixed ? std::max(1.2, 0.041 * N)
+                                               : std::max(C > 4 ? 2.3 : 1.7, (C > 4 ? 0.075 : 0.058) * N);
+  return us * n_exp;
 }
 
 double hmc_launch_us(const HmcArgs& a) {

@@ -33,6 +33,16 @@ def test_estimate_is_near_what_was_measured(us, case):
     assert 0.75 < us(N, chains, n_exp, 1, form) / MEASURED[case] < 1.25
 
 
+SPLIT = {(41, 2): 1.56, (53, 2): 1.73, (73, 2): 2.65, (101, 2): 4.1, (41, 4): 1.65, (53, 4): 1.81, (73, 4): 2.10,
+         (101, 4): 2.91}
+
+
+@pytest.mark.parametrize("N,waves", SPLIT)
+def test_estimate_of_chains_over_several_waves(us, N, waves):
+    """The waves share a chain's pairs, not what each of them repeats."""
+    assert 0.75 < us(N, 1, 1, waves, FIXED) / SPLIT[N, waves] < 1.25
+
+
 def test_order(us):
     for chains in (1, 4, 8):
         assert all(us(n + 1, chains) >= us(n, chains) for n in range(8, 128))
