@@ -195,9 +195,11 @@ int64_t hmc_team_waves(const HmcArgs& a);
 // Whether an advance launch of several steps is one by teams.
 bool hmc_runs_teams(const HmcArgs& a);
 // Duration of an evaluation of a galaxy's chains alone, and per evaluation of an
-// advance launch, us, about: what a call's launches are placed on streams by.
+// advance launch (of one of its galaxies' chains; of all), us, about: what a call's
+// launches are placed on streams by.
 enum class EvalForm : int { kGeneral, kFixed, kTeam };      // (kFixed: the kernels of one side)
 double hmc_eval_us(int N, int C, int n_exp, int wpc, EvalForm form);
+double hmc_chain_us(const HmcArgs& a);
 double hmc_launch_us(const HmcArgs& a);
 // Slot plans with a trajectory kernel specialised for stamp side N (0-terminated list of P).
 const int* hmc_fixed_plans(int N);

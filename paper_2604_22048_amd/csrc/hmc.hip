@@ -1746,14 +1746,18 @@ double hmc_eval_us(int N, int C, int n_exp, int wpc, EvalForm form) {
   return us * n_exp;
 }
 
-double hmc_launch_us(const HmcArgs& a) {
+double hmc_chain_us(const HmcArgs& a) {
   bool fixed = false;
   for (const int* p = hmc_fixed_plans(a.N); *p; ++p) fixed |= *p == a.P;
   fixed &= a.C <= 4 && a.prof != kProfGauss;
   const EvalForm form = hmc_runs_teams(a) ? EvalForm::kTeam : fixed ? EvalForm::kFixed : EvalForm::kGeneral;
-  const double waves = (double)a.n_gal * (a.C / launch_chains_per_wave(a, false)) * a.wpc;
   // (n_exp is set with mx only)
-  return hmc_eval_us(a.N, a.C, a.mx ? a.n_exp : 1, a.wpc, form) * std::max(1.0, waves / 1536.0);
+  return hmc_eval_us(a.N, a.C, a.mx ? a.n_exp : 1, a.wpc, form);
+}
+
+double hmc_launch_us(const HmcArgs& a) {
+  const double waves = (double)a.n_gal * (a.C / launch_chains_per_wave(a, false)) * a.wpc;
+  return hmc_chain_us(a) * std::max(1.0, waves / 1536.0);
 }
 
 template <int PROF, bool INIT>
